@@ -99,7 +99,7 @@ def cpu_baseline(shp, alpha):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2608_07974_amd", "csrc", "gemm.hip")
+GEMM_SOURCE = os.path.join(ROOT, "paper_2608_07974_amd", "csrc", "gemm_tiles.h")
 
 
 def measured_traffic(kernel, workload):

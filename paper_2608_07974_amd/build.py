@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "libzl.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["gemm.hip", "attention.hip", "attention_mfma.hip", "rowops.hip",
+SOURCES = ["gemm_kk.hip", "gemm_kn.hip", "gemm_mn.hip", "gemm_mk.hip", "gemm_f32.hip",
+           "gemm.hip", "attention.hip", "attention_mfma.hip", "rowops.hip",
            "objective.hip", "optim.hip", "zl.cpp", "runtime.cpp", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,7 +31,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # Hot kernels must not use scratch memory: a spill or an argument block
 # copied to scratch costs far more than any schedule gains (checked from the
 # compiler's resource-usage remarks).
-NO_SCRATCH = {"gemm.hip": "gemm_dma_kernel", "attention_mfma.hip": "attn_"}
+NO_SCRATCH = {"gemm_kk.hip": "gemm_dma_kernel", "gemm_kn.hip": "gemm_dma_kernel",
+              "gemm_mn.hip": "gemm_dma_kernel", "gemm_mk.hip": "gemm_dma_kernel",
+              "attention_mfma.hip": "attn_"}
 
 
 def _scratch_users(stderr, pattern):

@@ -1,0 +1,9 @@
+// The GEMM kernels of one operand layout (A K-major, B MN-major): a file each, so that they
+// compile in parallel.
+#include "gemm_tiles.h"
+
+namespace zl {
+
+template hipError_t run_layout<true, false>(const GemmDesc&, const EpiArgs&, hipStream_t, const char**);
+
+}  // namespace zl
