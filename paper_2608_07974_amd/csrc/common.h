@@ -159,12 +159,15 @@ hipError_t launch_head_norm(bool layernorm, const float* xa, const float* xb, in
                             hipStream_t s);
 // Norm backward: dx = dres + norm_bwd(dy) (dres may be nullptr; dx may alias
 // dres); also dx_act = act-dtype copy of dx when non-null.  Per-block
-// partial sums of dy*xhat (and dy) go to part_w/part_b [nblk, d].  When dx
-// is nullptr only the partials are formed.  Returns nblk via *nblk_out.
+// partial sums of dy*xhat (and dy) go to part_w/part_b [nblk, d]; with a
+// LayerNorm also those of dx to part_x when non-null (the gradient of a bias
+// that was added to the norm's input).  When dx is nullptr only part_w and
+// part_b are formed.  Returns nblk via *nblk_out.
 hipError_t launch_norm_bwd(bool layernorm, const float* dy, const float* x, const float* w,
                            const float* mean, const float* rstd, const float* dres,
                            float* dx, void* dx_act, int act_dtype, float* part_w,
-                           float* part_b, int T, int d, hipStream_t s, int* nblk_out);
+                           float* part_b, float* part_x, int T, int d, hipStream_t s,
+                           int* nblk_out);
 int norm_bwd_blocks(int T);
 // Head-norm backward for a row block: dh[row0 + i] = norm_bwd(dy[i]) (head
 // frozen, no weight gradient).  Also writes an act copy.
@@ -172,10 +175,11 @@ hipError_t launch_head_norm_bwd(bool layernorm, const float* dy, int64_t lddy, c
                                 const float* w, const float* mean, const float* rstd,
                                 int rstd_stride, float* dx, void* dx_act, int act_dtype,
                                 int row0, int rows, int d, hipStream_t s);
-// out[j] = (accumulate ? out[j] : 0) + scale * sum_b part[b, j]; part is
-// scratch (a first stage may overwrite some of its rows).
-hipError_t launch_reduce_rows(float* part, int nblk, int d, float* out, float scale,
-                              int accumulate, hipStream_t s);
+// out[i][j] = (accumulate ? out[i][j] : 0) + scale * sum_b part[i][b, j] for
+// i < np (1 to 3); part is scratch (a first stage may overwrite some of its
+// rows).
+hipError_t launch_reduce_rows(float* const* part, float* const* out, int np, int nblk, int d,
+                              float scale, int accumulate, hipStream_t s);
 // Column sums of an act-dtype matrix [T, n] into partials [nblk, n].
 hipError_t launch_colsum_partial(const void* x, int64_t ldx, int dtype, int T, int n,
                                  float* part, int* nblk_out, hipStream_t s);

@@ -132,49 +132,73 @@ hipError_t launch_head_norm(bool layernorm, const float* xa, const float* xb, in
 // sum(dy)) of the block's rows stay in registers and are written as one
 // row of part_w / part_b per block: deterministic, no atomics.
 int norm_bwd_blocks(int T) {
-  int blocks = T / 16;  // about 16 rows per block
+  // two blocks per CU from 4096 rows up (8 rows each), then 16 rows each
+  int blocks = T / 8 < 512 ? T / 8 : 512;
+  if (T / 16 > blocks) blocks = T / 16;
   if (blocks < 256) blocks = T < 256 ? T : 256;
   if (blocks > 2048) blocks = 2048;
   return blocks > 0 ? blocks : 1;  // number of partial rows
 }
 
-template <int CM, bool LN>
+template <int CM, bool LN, bool PF>
 __global__ void __launch_bounds__(RT)
 norm_bwd_kernel(const float* __restrict__ dy, int64_t lddy, const float* __restrict__ x,
                 const float* __restrict__ w, const float* __restrict__ mean,
                 const float* __restrict__ rstd, int rstride, const float* dres, float* dx,
                 void* dx_act, int adt, float* __restrict__ part_w, float* __restrict__ part_b,
-                int T, int d, int rpb, int nblk, int row_out0) {
+                float* __restrict__ part_x, int T, int d, int rpb, int nblk, int row_out0) {
   __shared__ float red[2][2][RT / 64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const bool want_part = part_w != nullptr;
-  float4 wv[CM], aw[CM], ab[CM];
+  float4 wv[CM], aw[CM], ab[CM], ax[CM];
 #pragma unroll
   for (int k = 0; k < CM; ++k) {
     const int c = (k * RT + tid) * 4;
     wv[k] = c < d ? *reinterpret_cast<const float4*>(w + c) : make_float4(0.f, 0.f, 0.f, 0.f);
     aw[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     ab[k] = aw[k];
+    ax[k] = aw[k];
   }
-  const int r0 = blockIdx.x * rpb, r1 = min(T, r0 + rpb);
+  const int r0 = blockIdx.x * rpb, r1 = blockIdx.x < nblk ? min(T, r0 + rpb) : r0;
+  // PF: dy, x, dres of the next row are loaded while this one is reduced: a
+  // row is a chain of load, block reduction and store, and with one or two
+  // blocks per CU nothing else hides it (4096 rows of 768: 27 -> 17 us; 8192 of
+  // 2048: 72 -> 50).  With four blocks per CU they hide each other and the
+  // registers of the next row cost occupancy (16384 of 4096: 225 -> 235).
+  float4 na[CM], nx[CM], nq[CM];
+  float nrs = 0.f, nmu = 0.f;
+  auto fetch = [&](int r) __attribute__((always_inline)) {
+    nrs = rstd[(int64_t)r * rstride];
+    nmu = LN ? mean[(int64_t)r * rstride] : 0.f;
+#pragma unroll
+    for (int k = 0; k < CM; ++k) {
+      const int c = (k * RT + tid) * 4;
+      na[k] = nx[k] = nq[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c >= d) continue;
+      const int64_t o = (int64_t)(row_out0 + r) * d + c;
+      na[k] = *reinterpret_cast<const float4*>(dy + (int64_t)r * lddy + c);
+      nx[k] = *reinterpret_cast<const float4*>(x + o);
+      if (dres) nq[k] = *reinterpret_cast<const float4*>(dres + o);
+    }
+  };
+  if (PF && r0 < r1) fetch(r0);
   int par = 0;
-  for (int r = (blockIdx.x < nblk ? r0 : T); r < r1; ++r) {
-    const float rs = rstd[(int64_t)r * rstride];
-    const float mu = LN ? mean[(int64_t)r * rstride] : 0.f;
+  for (int r = r0; r < r1; ++r) {
+    if (!PF) fetch(r);
+    const float rs = nrs, mu = nmu;
     const int ro = row_out0 + r;
-    const float* dyr = dy + (int64_t)r * lddy;
-    const float* xr = x + (int64_t)ro * d;
-    float4 av[CM], hv[CM];
+    float4 av[CM], hv[CM], qv[CM];
     float sg = 0.f, sgx = 0.f;
 #pragma unroll
     for (int k = 0; k < CM; ++k) {
       const int c = (k * RT + tid) * 4;
-      if (c >= d) { av[k] = make_float4(0.f, 0.f, 0.f, 0.f); hv[k] = av[k]; continue; }
-      const float4 a = *reinterpret_cast<const float4*>(dyr + c);
-      const float4 v = *reinterpret_cast<const float4*>(xr + c);
+      const float4 a = na[k], v = nx[k];
+      qv[k] = nq[k];
+      av[k] = a;
+      hv[k] = a;
+      if (c >= d) continue;
       const float4 g = wv[k];
       const float4 h = make_float4((v.x - mu) * rs, (v.y - mu) * rs, (v.z - mu) * rs, (v.w - mu) * rs);
-      av[k] = a;
       hv[k] = h;
       const float g0 = a.x * g.x, g1 = a.y * g.y, g2 = a.z * g.z, g3 = a.w * g.w;
       sg += (g0 + g1) + (g2 + g3);
@@ -184,6 +208,7 @@ norm_bwd_kernel(const float* __restrict__ dy, int64_t lddy, const float* __restr
         if (LN) { ab[k].x += a.x; ab[k].y += a.y; ab[k].z += a.z; ab[k].w += a.w; }
       }
     }
+    if (PF && r + 1 < r1) fetch(r + 1);
     if (!dx) continue;
     sg = wave_sum(sg);
     sgx = wave_sum(sgx);
@@ -205,14 +230,12 @@ norm_bwd_kernel(const float* __restrict__ dy, int64_t lddy, const float* __restr
     for (int k = 0; k < CM; ++k) {
       const int c = (k * RT + tid) * 4;
       if (c >= d) continue;
-      const float4 a = av[k], h = hv[k], g = wv[k];
+      const float4 a = av[k], h = hv[k], g = wv[k], q = qv[k];
       float o[4] = {rs * (a.x * g.x - mg - h.x * mgx), rs * (a.y * g.y - mg - h.y * mgx),
                     rs * (a.z * g.z - mg - h.z * mgx), rs * (a.w * g.w - mg - h.w * mgx)};
       const int64_t off = (int64_t)ro * d + c;
-      if (dres) {
-        const float4 q = *reinterpret_cast<const float4*>(dres + off);
-        o[0] += q.x; o[1] += q.y; o[2] += q.z; o[3] += q.w;
-      }
+      if (dres) { o[0] += q.x; o[1] += q.y; o[2] += q.z; o[3] += q.w; }
+      if (LN && part_x) { ax[k].x += o[0]; ax[k].y += o[1]; ax[k].z += o[2]; ax[k].w += o[3]; }
       *reinterpret_cast<float4*>(dx + off) = make_float4(o[0], o[1], o[2], o[3]);
       if (dx_act) {
         if (adt == BF16)
@@ -230,6 +253,7 @@ norm_bwd_kernel(const float* __restrict__ dy, int64_t lddy, const float* __restr
       if (c >= d) continue;
       *reinterpret_cast<float4*>(part_w + (int64_t)blockIdx.x * d + c) = aw[k];
       if (LN && part_b) *reinterpret_cast<float4*>(part_b + (int64_t)blockIdx.x * d + c) = ab[k];
+      if (LN && part_x) *reinterpret_cast<float4*>(part_x + (int64_t)blockIdx.x * d + c) = ax[k];
     }
   }
 }
@@ -238,24 +262,27 @@ template <int CM, bool LN>
 static void norm_bwd_go(int blocks, hipStream_t s, const float* dy, int64_t lddy, const float* x,
                         const float* w, const float* mean, const float* rstd, int rstride,
                         const float* dres, float* dx, void* dx_act, int adt, float* part_w,
-                        float* part_b, int T, int d, int rpb, int nb, int row_out0) {
-  hipLaunchKernelGGL((norm_bwd_kernel<CM, LN>), dim3(blocks), dim3(RT), 0, s, dy, lddy, x, w,
-                     mean, rstd, rstride, dres, dx, dx_act, adt, part_w, part_b, T, d, rpb, nb,
-                     row_out0);
+                        float* part_b, float* part_x, int T, int d, int rpb, int nb,
+                        int row_out0) {
+  // fewer than four blocks per CU, more than one row each
+  auto kern = blocks < 1024 && rpb > 1 ? norm_bwd_kernel<CM, LN, true> : norm_bwd_kernel<CM, LN, false>;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(RT), 0, s, dy, lddy, x, w, mean, rstd, rstride, dres,
+                     dx, dx_act, adt, part_w, part_b, part_x, T, d, rpb, nb, row_out0);
 }
 
 static hipError_t norm_bwd_launch(bool layernorm, const float* dy, int64_t lddy, const float* x,
                                   const float* w, const float* mean, const float* rstd,
                                   int rstride, const float* dres, float* dx, void* dx_act,
-                                  int adt, float* part_w, float* part_b, int T, int d,
-                                  int row_out0, int* nblk_out, hipStream_t s) {
-  const int nb = norm_bwd_blocks(T);
+                                  int adt, float* part_w, float* part_b, float* part_x, int T,
+                                  int d, int row_out0, int* nblk_out, hipStream_t s) {
+  // without partial sums to add up, as few rows per block as 2048 blocks allow
+  const int nb = part_w ? norm_bwd_blocks(T) : (T < 2048 ? T : 2048);
   const int rpb = (T + nb - 1) / nb;
   if (nblk_out) *nblk_out = nb;
   if (d <= 0 || d % 4 || d > 8192) return hipErrorInvalidValue;
 #define ZL_NB(CM, LN)                                                                       \
   norm_bwd_go<CM, LN>(nb, s, dy, lddy, x, w, mean, rstd, rstride, dres, dx, dx_act, adt,     \
-                      part_w, part_b, T, d, rpb, nb, row_out0)
+                      part_w, part_b, part_x, T, d, rpb, nb, row_out0)
   const int cm = (d + 4 * RT - 1) / (4 * RT);
   if (layernorm) {
     if (cm <= 1) ZL_NB(1, true);
@@ -275,9 +302,10 @@ static hipError_t norm_bwd_launch(bool layernorm, const float* dy, int64_t lddy,
 hipError_t launch_norm_bwd(bool layernorm, const float* dy, const float* x, const float* w,
                            const float* mean, const float* rstd, const float* dres,
                            float* dx, void* dx_act, int act_dtype, float* part_w,
-                           float* part_b, int T, int d, hipStream_t s, int* nblk_out) {
+                           float* part_b, float* part_x, int T, int d, hipStream_t s,
+                           int* nblk_out) {
   return norm_bwd_launch(layernorm, dy, (int64_t)d, x, w, mean, rstd, 1, dres, dx, dx_act,
-                         act_dtype, part_w, part_b, T, d, 0, nblk_out, s);
+                         act_dtype, part_w, part_b, part_x, T, d, 0, nblk_out, s);
 }
 
 hipError_t launch_head_norm_bwd(bool layernorm, const float* dy, int64_t lddy, const float* x,
@@ -286,64 +314,80 @@ hipError_t launch_head_norm_bwd(bool layernorm, const float* dy, int64_t lddy, c
                                 int row0, int rows, int d, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   return norm_bwd_launch(layernorm, dy, lddy, x, w, mean, rstd, rstd_stride, nullptr, dx, dx_act,
-                         act_dtype, nullptr, nullptr, rows, d, row0, nullptr, s);
+                         act_dtype, nullptr, nullptr, nullptr, rows, d, row0, nullptr, s);
 }
 
 // ------------------------------------------------------------- reductions
-// out[j] = (accumulate ? out[j] : 0) + scale * sum_b part[b, j]; a block
-// covers 64 columns with 4 row groups, each summing with 4 independent
-// accumulators; the 4 group sums combine in a fixed order (deterministic).
+// out[j] = (accumulate ? out[j] : 0) + scale * sum_b part[b, j] for up to
+// three (part, out) pairs of the same shape (grid z).  A block covers 32
+// columns with 32 row groups of 8 rows in flight each, so up to 256 rows are
+// one memory round trip (64 columns x 4 groups with 4 in flight took 7.3 us for
+// 256 x 768: 16 round trips); the group sums combine in a fixed order.
 // Rows b < nblk of part at part + b * rstride.  Block (x, y) sums rows
-// [y gs, min(nblk, (y + 1) gs)) of columns 64 x .. 64 x + 63 in a fixed
-// order; the last stage (final) writes out, an earlier one leaves its sum in
-// place of the group's first row (read by the next stage), so the result is
-// deterministic for a given nblk.
-__global__ void __launch_bounds__(256) reduce_rows_kernel(float* part, int nblk, int64_t rstride,
-                                                          int d, int gs, float* __restrict__ out,
-                                                          float scale, int accumulate, int final) {
-  __shared__ float red[4][64];
-  const int j = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int grp = threadIdx.x >> 6;
+// [y gs, min(nblk, (y + 1) gs)) of its columns in a fixed order; the last
+// stage (final) writes out, an earlier one leaves its sum in place of the
+// group's first row (read by the next stage), so the result is deterministic
+// for a given nblk.
+struct ReduceArgs {
+  float* part[3];
+  float* out[3];
+};
+__global__ void __launch_bounds__(1024) reduce_rows_kernel(ReduceArgs ra, int nblk, int64_t rstride,
+                                                           int d, int gs, float scale,
+                                                           int accumulate, int final) {
+  __shared__ float red[32][33];
+  float* part = ra.part[blockIdx.z];
+  const int cl = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int j = blockIdx.x * 32 + cl;
   const int b0 = blockIdx.y * gs, b1 = min(nblk, b0 + gs);
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+  float t = 0.f;
   if (j < d) {
-    int b = b0 + grp;
-    for (; b + 12 < b1; b += 16) {
-      a0 += part[(int64_t)b * rstride + j];
-      a1 += part[(int64_t)(b + 4) * rstride + j];
-      a2 += part[(int64_t)(b + 8) * rstride + j];
-      a3 += part[(int64_t)(b + 12) * rstride + j];
+    for (int b = b0 + grp; b < b1; b += 256) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = b + 32 * k < b1 ? part[(int64_t)(b + 32 * k) * rstride + j] : 0.f;
+      t += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
-    for (; b < b1; b += 4) a0 += part[(int64_t)b * rstride + j];
   }
-  red[grp][threadIdx.x & 63] = (a0 + a1) + (a2 + a3);
+  red[grp][cl] = t;
   __syncthreads();
   if (grp == 0 && j < d) {
-    const float t = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 32; ++k) a[k & 3] += red[k][cl];
+    const float sum = (a[0] + a[1]) + (a[2] + a[3]);
     if (final) {
-      const float v = scale * t;
+      float* out = ra.out[blockIdx.z];
+      const float v = scale * sum;
       out[j] = accumulate ? out[j] + v : v;
     } else {
-      part[(int64_t)b0 * rstride + j] = t;
+      part[(int64_t)b0 * rstride + j] = sum;
     }
   }
 }
 
-hipError_t launch_reduce_rows(float* part, int nblk, int d, float* out, float scale,
-                              int accumulate, hipStream_t s) {
+hipError_t launch_reduce_rows(float* const* part, float* const* out, int np, int nblk, int d,
+                              float scale, int accumulate, hipStream_t s) {
   if (d <= 0) return hipSuccess;
-  const int cb = (d + 63) / 64;
+  if (np < 1 || np > 3) return hipErrorInvalidValue;
+  ReduceArgs ra;
+  for (int i = 0; i < 3; ++i) {
+    ra.part[i] = part[i < np ? i : 0];
+    ra.out[i] = out[i < np ? i : 0];
+  }
+  const int cb = (d + 31) / 32;
   int64_t stride = d;
-  if (nblk > 256) {  // first stage: groups of 64 rows, many blocks
+  if (nblk > 512) {  // first stage: groups of 64 rows, many blocks
     constexpr int GS = 64;
     const int ng = (nblk + GS - 1) / GS;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(cb, ng), dim3(256), 0, s, part, nblk, stride, d,
-                       GS, out, scale, accumulate, 0);
+    hipLaunchKernelGGL(reduce_rows_kernel, dim3(cb, ng, np), dim3(1024), 0, s, ra, nblk, stride, d,
+                       GS, scale, accumulate, 0);
     nblk = ng;
     stride *= GS;
   }
-  hipLaunchKernelGGL(reduce_rows_kernel, dim3(cb, 1), dim3(256), 0, s, part, nblk, stride, d, nblk,
-                     out, scale, accumulate, 1);
+  hipLaunchKernelGGL(reduce_rows_kernel, dim3(cb, 1, np), dim3(1024), 0, s, ra, nblk, stride, d,
+                     nblk, scale, accumulate, 1);
   return hipGetLastError();
 }
 

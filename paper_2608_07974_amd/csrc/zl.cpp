@@ -329,7 +329,8 @@ void build_plan(const zl_config& c, Plan& p) {
   p.DO = take(T * m.dq * act);
   p.DQKV = take(T * m.nqkv * act);
   p.DELTA = take(T * m.hq * 4);
-  size_t pe = (size_t)2 * norm_bwd_blocks((int)T) * m.d;
+  // partial rows of the norm backward: dgamma, and with a LayerNorm dbeta and dx
+  size_t pe = (size_t)(m.llama ? 1 : 3) * norm_bwd_blocks((int)T) * m.d;
   size_t widest = m.nqkv > m.ff ? m.nqkv : m.ff;
   if (m.d > (int)widest) widest = m.d;
   const size_t pc = (size_t)colsum_blocks((int)T) * widest;
@@ -954,7 +955,8 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
   void* DO = c->ws + p.DO;
   void* DQKV = c->ws + p.DQKV;
   float* PART = c->at<float>(p.PART);
-  const size_t half_part = p.part_elems / 2;
+  const size_t pn = (size_t)norm_bwd_blocks(T) * m.d;
+  float* const nparts[3] = {PART, PART + pn, PART + 2 * pn};  // dgamma, dbeta, dx
 
   auto wgrad = [&](int M, int N, const void* A, int64_t lda, const void* Bm, int64_t ldb,
                    size_t goff) -> hipError_t {
@@ -982,7 +984,8 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
     c->prof_stop(pi, s, "colsum", 0, (double)T * n * (dt == BF16 ? 2 : 4));
     if (e != hipSuccess) return e;
     pi = c->prof_start(s);
-    e = launch_reduce_rows(PART, nblk, n, c->G(goff), grad_scale, acc, s);
+    float* out = c->G(goff);
+    e = launch_reduce_rows(&PART, &out, 1, nblk, n, grad_scale, acc, s);
     c->prof_stop(pi, s, "reduce_rows", 0, 0);
     return e;
   };
@@ -1049,7 +1052,9 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
     if (r) {
       ZL_HIP(lora_bwd_w(DXA, m.d, c->ws + p.ACT[l], m.ff, lo->down_a, r, c->ws + p.LXD[l],
                         lo->down_b, w_d, 1));
-    } else if (ln) {  // the down weight gradient runs with the QKV one below
+    } else if (ln && l == m.L - 1) {
+      // the down weight gradient runs with the QKV one below; below the top
+      // layer the bias gradient came with the norm-1 backward of the layer above
       ZL_HIP(bias_grad(DX, F32, m.d, o.b_down));
     }
     // up projection (gate|up or fc)
@@ -1072,11 +1077,12 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
       int nblk = 0;
       ZL_RUN("norm_bwd", 0, (double)T * m.d * (16 + c->asz()), launch_norm_bwd(ln, DN, c->at<float>(p.X2[l]), c->V32(o.ln2_w),
                              ln ? c->at<float>(p.MU2[l]) : nullptr, c->at<float>(p.RS2[l]), DX, DX,
-                             DXB, act, r ? nullptr : PART, ln && !r ? PART + half_part : nullptr,
-                             T, m.d, s, &nblk));
+                             DXB, act, r ? nullptr : PART, ln && !r ? nparts[1] : nullptr,
+                             ln && !r ? nparts[2] : nullptr, T, m.d, s, &nblk));
       if (!r) {
-        ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(PART, nblk, m.d, c->G(o.ln2_w), grad_scale, acc, s));
-        if (ln) ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(PART + half_part, nblk, m.d, c->G(o.ln2_b), grad_scale, acc, s));
+        // the output projection's bias gradient is the column sum of dx
+        float* const outs[3] = {c->G(o.ln2_w), ln ? c->G(o.ln2_b) : nullptr, ln ? c->G(o.b_o) : nullptr};
+        ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(nparts, outs, ln ? 3 : 1, nblk, m.d, grad_scale, acc, s));
       }
     }
     // output projection; in bf16 its epilogue also forms the attention
@@ -1100,7 +1106,6 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
       // the output projection (dy = DXB)
       ZL_HIP(wgrad2(m.nup, m.d, DUP, m.nup, c->ws + p.N2[l], m.d, o.w_up,
                     m.d, m.dq, DXB, m.d, c->ws + p.O[l], m.dq, o.w_o));
-      if (ln) ZL_HIP(bias_grad(DX, F32, m.d, o.b_o));
     }
     // attention
     {
@@ -1157,10 +1162,14 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
       ZL_RUN("norm_bwd", 0, (double)T * m.d * (16 + c->asz()), launch_norm_bwd(ln, DN, c->at<float>(p.X[l]), c->V32(o.ln1_w),
                              ln ? c->at<float>(p.MU1[l]) : nullptr, c->at<float>(p.RS1[l]), dx, dx,
                              l > 0 ? DXA : nullptr, act, r ? nullptr : PART,
-                             ln && !r ? PART + half_part : nullptr, T, m.d, s, &nblk));
+                             ln && !r ? nparts[1] : nullptr, ln && !r && l > 0 ? nparts[2] : nullptr, T,
+                             m.d, s, &nblk));
       if (!r) {
-        ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(PART, nblk, m.d, c->G(o.ln1_w), grad_scale, acc, s));
-        if (ln) ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(PART + half_part, nblk, m.d, c->G(o.ln1_b), grad_scale, acc, s));
+        // dx is the gradient of the layer below's output: its column sum is that
+        // layer's down bias gradient
+        float* const outs[3] = {c->G(o.ln1_w), ln ? c->G(o.ln1_b) : nullptr,
+                                ln && l > 0 ? c->G(c->layout.lay[l - 1].b_down) : nullptr};
+        ZL_RUN("reduce_rows", 0, 0, launch_reduce_rows(nparts, outs, ln ? (l > 0 ? 3 : 2) : 1, nblk, m.d, grad_scale, acc, s));
       }
     }
   }
