@@ -16,7 +16,8 @@ OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "libzl.so")
 BUILD = os.path.join(ROOT, "_build")
 SOURCES = ["gemm_kk.hip", "gemm_kn.hip", "gemm_mn.hip", "gemm_mk.hip", "gemm_f32.hip",
-           "gemm.hip", "attention.hip", "attention_mfma.hip", "rowops.hip",
+           "gemm_skinny.hip", "gemm.hip",
+           "attention.hip", "attention_mfma.hip", "rowops.hip",
            "objective.hip", "optim.hip", "zl.cpp", "runtime.cpp", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

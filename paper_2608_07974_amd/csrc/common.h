@@ -144,6 +144,29 @@ hipError_t launch_gemm_pair(const GemmDesc& g1, const EpiArgs& e1, const GemmDes
                             const EpiArgs& e2, int dtype, hipStream_t s, bool* fused,
                             const char** kname = nullptr);
 
+// Up to three independent GEMMs of the same M in one launch, where each has few
+// output columns and a plain store; false if they do not all qualify (nothing
+// is launched; the caller runs launch_gemm on each).
+bool launch_gemm_group(const GemmDesc* g, const EpiArgs* e, int np, int dtype, hipStream_t s,
+                       hipError_t* err);
+
+// Gradients of low-rank factors: out[w ldw + n ldr] = (acc ? itself : 0) +
+// scale * sum_t Y[t, w] S[t, n], t < T, w < W, n < R; up to four in one launch
+// (act dtype operands).  part: optional scratch for splitting T.  False if they
+// do not qualify (bf16, R <= 64, aligned rows): nothing is launched.
+struct LowRankGrad {
+  const void* Y;
+  int64_t ldy;
+  int W;
+  const void* S;
+  int64_t lds;
+  int R;
+  float* out;
+  int64_t ldw, ldr;
+};
+bool launch_lowrank_grads(const LowRankGrad* p, int np, int T, float scale, int acc, float* part,
+                          size_t part_elems, int dtype, hipStream_t s, hipError_t* err);
+
 // --------------------------------------------------------------- row ops
 // Norm forward over rows: y = norm(x) * w (+ b).  x fp32 [T, d] (row stride
 // ldx); y in act dtype.  Writes rstd [T] (and mean [T] for LayerNorm).

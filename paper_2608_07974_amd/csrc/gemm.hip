@@ -86,6 +86,20 @@ template <bool AK, bool BKM>
 hipError_t run_pair_layout(const GemmDesc& g1, const EpiArgs& e1, const GemmDesc& g2,
                            const EpiArgs& e2, hipStream_t s, bool* fused);
 hipError_t launch_gemm_f32(const GemmDesc& g, const EpiArgs& e, hipStream_t s);
+// Up to three products of the same M and layout, few columns each (gemm_skinny.hip).
+bool skinny_ok(const GemmDesc& g, const EpiArgs& e);
+hipError_t launch_gemm_skinny(const GemmDesc* g, const EpiArgs* e, int np, hipStream_t s);
+
+bool launch_gemm_group(const GemmDesc* g, const EpiArgs* e, int np, int dtype, hipStream_t s,
+                       hipError_t* err) {
+  if (dtype != BF16 || np < 1 || np > 3) return false;
+  for (int i = 0; i < np; ++i)
+    if (g[i].M <= 0 || g[i].N <= 0 || g[i].M != g[0].M || g[i].b_kmajor != g[0].b_kmajor ||
+        !skinny_ok(g[i], e[i]))
+      return false;
+  *err = launch_gemm_skinny(g, e, np, s);
+  return true;
+}
 
 hipError_t launch_gemm_pair(const GemmDesc& g1, const EpiArgs& e1, const GemmDesc& g2,
                             const EpiArgs& e2, int dtype, hipStream_t s, bool* fused,
@@ -117,6 +131,10 @@ hipError_t launch_gemm(const GemmDesc& g, const EpiArgs& e, int dtype, hipStream
   if (dtype == F32) {
     if (kname) *kname = "gemm_f32_32x32";
     return launch_gemm_f32(g, e, s);
+  }
+  if (skinny_ok(g, e)) {
+    if (kname) *kname = "gemm_skinny";
+    return launch_gemm_skinny(&g, &e, 1, s);
   }
   if (g.a_kmajor && g.b_kmajor) return run_layout<true, true>(g, e, s, kname);
   if (g.a_kmajor && !g.b_kmajor) return run_layout<true, false>(g, e, s, kname);

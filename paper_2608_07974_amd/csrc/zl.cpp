@@ -1004,22 +1004,51 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
     hipError_t err = hipSuccess;
     int col = 0;
     size_t boff = b_off;
-    for (int j = 0; j < nblk && err == hipSuccess; ++j) {
-      EpiArgs ee = epi(EPI_STORE, static_cast<char*>(LE) + (size_t)j * r * asz, na, act);
-      ee.scale = m.ls;
-      err = run_gemm(c, s, gdesc(T, r, widths[j], static_cast<const char*>(dy) + (size_t)col * asz,
-                                 out, true, c->WT(boff), r, false), ee);
+    GemmDesc ge[3];
+    EpiArgs ee[3];
+    for (int j = 0; j < nblk; ++j) {
+      ee[j] = epi(EPI_STORE, static_cast<char*>(LE) + (size_t)j * r * asz, na, act);
+      ee[j].scale = m.ls;
+      ge[j] = gdesc(T, r, widths[j], static_cast<const char*>(dy) + (size_t)col * asz, out, true,
+                    c->WT(boff), r, false);
       col += widths[j];
       boff += (size_t)widths[j] * r;
+    }
+    const int pi = c->prof_start(s);
+    if (launch_gemm_group(ge, ee, nblk, act, s, &err)) {
+      c->prof_stop(pi, s, "gemm_skinny", 2.0 * T * r * col, 0.0);
+    } else {
+      c->prof_cancel(pi);
+      for (int j = 0; j < nblk && err == hipSuccess; ++j) err = run_gemm(c, s, ge[j], ee[j]);
     }
     if (need_dx) { g.K2 = na; g.A2 = LE; g.lda2 = na; g.B2 = c->WT(a_off); g.ldb2 = in; }
     return err;
   };
   auto lora_bwd_w = [&](const void* dy, int out, const void* x, int in, size_t a_off, int na,
                         const void* xa, size_t b_off, const int* widths, int nblk) -> hipError_t {
-    hipError_t err = wgrad(na, in, LE, na, x, in, a_off);
+    LowRankGrad lg[4];
+    lg[0] = {x, in, in, LE, na, na, c->G(a_off), 1, in};
+    double wide = (double)in * na;
     int col = 0;
     size_t boff = b_off;
+    for (int j = 0; j < nblk; ++j) {
+      lg[1 + j] = {static_cast<const char*>(dy) + (size_t)col * asz, out, widths[j],
+                   static_cast<const char*>(xa) + (size_t)j * r * asz, na, r, c->G(boff), r, 1};
+      wide += (double)widths[j] * r;
+      col += widths[j];
+      boff += (size_t)widths[j] * r;
+    }
+    hipError_t err = hipSuccess;
+    const int pi = c->prof_start(s);
+    if (launch_lowrank_grads(lg, 1 + nblk, T, grad_scale, acc,
+                             p.spk_elems ? c->at<float>(p.SPK) : nullptr, p.spk_elems, act, s, &err)) {
+      c->prof_stop(pi, s, "lowrank_grad", 2.0 * T * wide, 0.0);
+      return err;
+    }
+    c->prof_cancel(pi);
+    err = wgrad(na, in, LE, na, x, in, a_off);
+    col = 0;
+    boff = b_off;
     for (int j = 0; j < nblk && err == hipSuccess; ++j) {
       err = wgrad(widths[j], r, static_cast<const char*>(dy) + (size_t)col * asz, out,
                   static_cast<const char*>(xa) + (size_t)j * r * asz, na, boff);

@@ -309,3 +309,73 @@ def test_backward_pairs_weight_gradients():
     shp1 = workload.get_config("1b").with_(n_layers=1, batch=1, seq=512)
     launches = sum(e["launches"] for e in _backward_profile(shp1))
     assert launches == 4
+
+
+@pytest.mark.parametrize("b_k", [True, False])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (16, 16, 128), (17, 24, 1032), (1000, 40, 2048), (300, 64, 136),
+                                   (8200, 8, 520), (8200, 32, 264)])
+def test_gemm_few_columns(b_k, M, N, K):
+    """At most 64 output columns over a K-major A (the LoRA products): rows
+    past a block's 16 or 32, columns past 16 or 32, K past the waves' 128-wide
+    slices, all against fp64 within fp32 summation error."""
+    zl = _zl()
+    gen = torch.Generator(device=_dev()).manual_seed(M + N + K)
+    A = torch.randn(M, K, device=_dev(), generator=gen).to(torch.bfloat16)
+    B = torch.randn(*((N, K) if b_k else (K, N)), device=_dev(), generator=gen).to(torch.bfloat16)
+    C = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device=_dev())
+    torch.cuda.synchronize()
+    zl.zl_kernel_gemm(M, N, K, A.data_ptr(), K, True, B.data_ptr(), B.shape[1], b_k, C.data_ptr(), N,
+                      zl.ZL_BF16, _stream())
+    torch.cuda.synchronize()
+    ref = A.double().cpu() @ (B.t() if b_k else B).double().cpu()
+    assert bool(torch.isnan(C[M]).all())  # nothing written past the last row
+    assert rel_err(C[:M].cpu().double().numpy(), ref.numpy()) < 2e-6
+
+
+@pytest.mark.parametrize("arch,rank,B,S", [("1b", 4, 1, 37), ("1b", 16, 3, 700), ("1b", 24, 2, 65), ("gpt2", 8, 5, 203)])
+def test_lora_factor_gradients(arch, rank, B, S):
+    """Factor gradients of one LoRA layer, dB = dy^T xa and dA = E^T x with
+    xa = s x A^T and E = s dy B rounded to bf16 as stored, from the chunk's own
+    operands in fp64: token counts that are no multiple of a slice, split rows
+    (2100), three or two factors beside each other, and a rank whose stacked
+    QKV factors are too wide for the low-rank kernel (3 x 24 > 64).  The
+    recomputed operands may round differently where fp32 sums differ, half a
+    bf16 unit (2^-9) on few entries."""
+    import workload
+    from paper_2608_07974_amd.chunk import TorchChunk, config_from_shape
+    shp = workload.get_config(arch).with_(n_layers=1, batch=B, seq=S, lora_rank=rank)
+    cfg = config_from_shape(shp, alpha=1.0, optimizer="sgd")
+    ch = TorchChunk(cfg)
+    gen = torch.Generator(device=_dev()).manual_seed(rank + S)
+    ch.master.normal_(0.0, 0.02, generator=gen)
+    ch.base_master.normal_(0.0, 0.02, generator=gen)
+    ch.head_w.normal_(0.0, 0.02, generator=gen)
+    zl = _zl()
+    zl.zl_refresh_shadow(ch.handle, _stream())
+    h = torch.randn(B, S, shp.d_model, device=_dev(), generator=gen).to(torch.bfloat16)
+    lab = torch.randint(0, shp.vocab, (B, S), device=_dev(), generator=gen).to(torch.int32)
+    ch.forward(h)
+    ch.objective(lab)
+    ch.backward(1.0, 0)
+    s = cfg.lora_alpha / rank
+    llama = arch != "gpt2"
+    q, kv = shp.n_heads * shp.head_dim, shp.n_kv_heads * shp.head_dim
+    groups = [("n2", "dup", ["wg", "wu"] if llama else ["wfc"], [shp.d_ff] * (2 if llama else 1)),
+              ("act", "dxa", ["wd"] if llama else ["wproj"], [shp.d_model]),
+              ("o", "dxb", ["wo"], [shp.d_model]),
+              ("n1", "dqkv", ["wq", "wk", "wv"] if llama else ["wqkv"], [q, kv, kv] if llama else [q + 2 * kv])]
+    for xn, dyn, names, widths in groups:
+        x, dy = ch.inspect_device(xn).double(), ch.inspect_device(dyn).double()
+        col = 0
+        for name, w in zip(names, widths):
+            a = ch.view(ch.shadow, f"L0.{name}_la").double()
+            b = ch.view(ch.shadow, f"L0.{name}_lb").double()
+            d = dy[:, col: col + w]
+            xa = (s * (x @ a.t())).to(torch.bfloat16).double()
+            e = (s * (d @ b)).to(torch.bfloat16).double()
+            for key, ref in ((f"L0.{name}_lb", d.t() @ xa), (f"L0.{name}_la", e.t() @ x)):
+                got = ch.view(ch.grad, key).double()
+                assert bool(torch.isfinite(got).all()), key
+                assert float((got - ref).norm() / ref.norm()) < 1e-3, key
+            col += w
+    ch.close()
