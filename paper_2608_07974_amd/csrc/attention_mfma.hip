@@ -412,24 +412,42 @@ __global__ void __launch_bounds__(FW_NT) attn_fwd_mfma(AttnDesc a) {
 }
 
 // ------------------------------------------------------------------ delta
-// delta[b, h, i] = sum_d dO[i, h, d] * O[i, h, d]; one wave per (row, head).
-template <int HD>
+// delta[b, h, i] = sum_d dO[i, h, d] * O[i, h, d].  HD / 8 lanes per head read
+// 8 columns each (16 bytes), neighbouring heads of a row side by side: bound by
+// reading O and dO.  (A wave per row and head with 2-byte loads took 154 us,
+// 1.7 TB/s, at 16384 x 32 x 128.)  DL_ROWS rows in flight per lane: four where
+// that still gives four blocks per CU, else one (a launch of a few hundred rows
+// is one memory round trip either way, and more blocks start it sooner).
+template <int HD, int DL_ROWS>
 __global__ void __launch_bounds__(256) attn_delta_mfma(AttnDesc a) {
-  const int64_t w = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  const int64_t n = (int64_t)a.B * a.Hq * a.S;
-  if (w >= n) return;
-  const int i = (int)(w % a.S);
-  const int h = (int)((w / a.S) % a.Hq);
-  const int b = (int)(w / ((int64_t)a.S * a.Hq));
-  const int64_t row = (int64_t)b * a.S + i;
-  const bf16_t* O = reinterpret_cast<const bf16_t*>(a.o) + row * a.ldo + (int64_t)h * HD;
-  const bf16_t* D = reinterpret_cast<const bf16_t*>(a.dout) + row * a.lddo + (int64_t)h * HD;
-  float s = 0.f;
-  for (int d = lane; d < HD; d += 64) s += bf16_to_f32(O[d]) * bf16_to_f32(D[d]);
+  constexpr int LPH = HD / 8;
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int part = (int)(t % LPH), h = (int)(t / LPH % a.Hq);
+  const int64_t r0 = t / ((int64_t)LPH * a.Hq) * DL_ROWS, rows = (int64_t)a.B * a.S;
+  const int64_t col = (int64_t)h * HD + part * 8;
+  uint4 o[DL_ROWS], d[DL_ROWS];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) a.delta[((int64_t)b * a.Hq + h) * a.S + i] = s;
+  for (int k = 0; k < DL_ROWS; ++k) {
+    const int64_t r = min(r0 + k, rows - 1);
+    o[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(a.o) + r * a.ldo + col);
+    d[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(a.dout) + r * a.lddo + col);
+  }
+#pragma unroll
+  for (int k = 0; k < DL_ROWS; ++k) {
+    const uint32_t x[4] = {o[k].x, o[k].y, o[k].z, o[k].w}, y[4] = {d[k].x, d[k].y, d[k].z, d[k].w};
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      s += bf16_to_f32((bf16_t)(x[i] & 0xffff)) * bf16_to_f32((bf16_t)(y[i] & 0xffff)) +
+           bf16_to_f32((bf16_t)(x[i] >> 16)) * bf16_to_f32((bf16_t)(y[i] >> 16));
+#pragma unroll
+    for (int off = 1; off < LPH; off <<= 1) s += __shfl_xor(s, off, 64);
+    const int64_t r = r0 + k;
+    if (part == 0 && r < rows) {
+      const int64_t b = r / a.S;
+      a.delta[(b * a.Hq + h) * a.S + (r - b * a.S)] = s;
+    }
+  }
 }
 
 // ------------------------------------------------------------------- dK dV
@@ -868,10 +886,14 @@ static hipError_t bwd(const AttnDesc& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     once = true;
   }
-  const int64_t rows = (int64_t)a.B * a.Hq * a.S;
   if (!a.delta_ready) {
-    hipLaunchKernelGGL(attn_delta_mfma<HD>, dim3((unsigned)((rows * 64 + 255) / 256)), dim3(256), 0,
-                       s, a);
+    const int64_t rows = (int64_t)a.B * a.S, per = (int64_t)a.Hq * (HD / 8);
+    if (rows * per >= 4 * 256 * 1024)
+      hipLaunchKernelGGL((attn_delta_mfma<HD, 4>), dim3((unsigned)(((rows + 3) / 4 * per + 255) / 256)),
+                         dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((attn_delta_mfma<HD, 1>), dim3((unsigned)((rows * per + 255) / 256)), dim3(256),
+                         0, s, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
