@@ -113,6 +113,15 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
   // a0: the 32 rows' accumulators (MF 32), or those of their first 16 rows
   // with a1 those of the second 16 (MF 16)
   auto chunk = [&](const acc_t (&a0)[FN], const acc_t (&a1)[FN], const int i) __attribute__((always_inline)) {
+    // EPI_LOGITS: the labels of the chunk's rows (of its z rows when paired), one
+    // per lane, loaded once; a load per column group would wait a memory round
+    // trip behind the previous group's stores
+    int lab = -1;
+    if (e.kind == EPI_LOGITS && e.zy) {
+      const int r0 = m0 + wm * TM + i * 32;
+      const int m = e.pair ? r0 + 2 * (lane & 15) : r0 + (lane & 31);
+      if (m < g.M) lab = e.lab[e.pair ? m >> 1 : m];
+    }
 #pragma unroll
     for (int h = 0; h < 32 / MF; ++h)
 #pragma unroll
@@ -248,11 +257,18 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
     } else if (e.kind == EPI_LOGITS) {
       // 8 lanes cover a 64-column block of one row (64 % EW == 0, TN % 64 == 0)
       static_assert(TN % 64 == 0, "logit statistics need 64-column blocks");
+      // Columns past N count as -inf (only a wave's last columns can be).
+      const bool cut = nb + TN > g.N;
+      auto mask_cols = [&](const int n, float (&v)[EW]) __attribute__((always_inline)) {
+        if (cut)
+#pragma unroll
+          for (int k = 0; k < EW; ++k) v[k] = n + k < g.N ? v[k] : -INFINITY;
+      };
       // The maximum of one row's 64-column block (every lane of the 8 gets it).
-      auto block_max = [&](const int n, const float (&v)[EW]) __attribute__((always_inline)) {
+      auto block_max = [&](const float (&v)[EW]) __attribute__((always_inline)) {
         float mx = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < EW; ++k) mx = n + k < g.N ? fmaxf(mx, v[k]) : mx;
+        for (int k = 0; k < EW; ++k) mx = fmaxf(mx, v[k]);
         static_assert(64 / EW == 8, "a 64-column block spans 8 lanes");
         return max8(mx);
       };
@@ -266,7 +282,10 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
           float r[EW];
 #pragma unroll
           for (int k = 0; k < EW; ++k) r[k] = v[k] - mx;
-          epilogue_v(e, g.M, g.N, m, n, r, vec);
+          if (vec && m < g.M && n + EW <= g.N)
+            stv_f16_neg(e.out, (size_t)m * e.ldo + n, r);
+          else
+            epilogue_v(e, g.M, g.N, m, n, r, vec);
         } else {
           epilogue_v(e, g.M, g.N, m, n, v, vec);
         }
@@ -281,7 +300,7 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
           const float nm = -mx * L2E;
 #pragma unroll
           for (int k = 0; k < EW; ++k) {
-            const float p = n + k < g.N ? __builtin_amdgcn_exp2f(__builtin_fmaf(v[k], L2E, nm)) : 0.f;
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(v[k], L2E, nm));
             sp.s += p;
             sp.e += p * w[k];
           }
@@ -291,15 +310,16 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
         if ((lane & (64 / EW - 1)) == 0 && m < g.M && n < g.N)
           e.stats[(int64_t)m * e.ldst + n / 64] = make_float4(sp.m, sp.s, sp.e, 0.f);
       };
-      // the label's logit of a z row, in fp32 (the cache may be fp16)
-      auto label_logit = [&](const int m, const int n, const float (&v)[EW])
+      // the label's logit of a z row, in fp32 (the cache may be fp16): one test
+      // per 8 columns
+      auto label_logit = [&](const int m, const int n, const int y, const float (&v)[EW])
           __attribute__((always_inline)) {
-        if (e.zy && m < g.M) {
-          const int tok = e.pair ? m >> 1 : m;
-          const int y = e.lab[tok];
+        if (e.zy && m < g.M && (y & ~(EW - 1)) == n) {
+          // stores under constant indices: a select over v would put it in scratch
+          float* z = e.zy + (e.pair ? m >> 1 : m);
 #pragma unroll
           for (int k = 0; k < EW; ++k)
-            if (y == n + k) e.zy[tok] = v[k];
+            if (y == n + k) *z = v[k];
         }
       };
       if (e.pair) {
@@ -323,10 +343,12 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
             w[k] = v[k] - u[k];
             wn[k] = -w[k];
           }
-          const float mv = block_max(n, v), mu = block_max(n, u);
+          mask_cols(n, v);
+          mask_cols(n, u);
+          const float mv = block_max(v), mu = block_max(u);
           store_logits(m, n, v, mv);
           store_logits(m + 1, n, u, mu);
-          label_logit(m, n, v);
+          label_logit(m, n, __shfl(lab, row >> 1, 64), v);
           block_stats(m, n, v, w, mv);
           block_stats(m + 1, n, u, wn, mu);
         }
@@ -340,10 +362,14 @@ __device__ __forceinline__ void store_tile(const typename Mma<MF>::acc_t (&acc)[
             const float4 x = *reinterpret_cast<const float4*>(&ep[row * LDW + col + k]);
             v[k] = x.x; v[k + 1] = x.y; v[k + 2] = x.z; v[k + 3] = x.w;
           }
-          const float mv = block_max(n, v);
+          float w[EW];
+#pragma unroll
+          for (int k = 0; k < EW; ++k) w[k] = v[k];
+          mask_cols(n, v);
+          const float mv = block_max(v);
           store_logits(m, n, v, mv);
-          label_logit(m, n, v);
-          block_stats(m, n, v, v, mv);
+          label_logit(m, n, __shfl(lab, row, 64), v);
+          block_stats(m, n, v, w, mv);
         }
       }
     } else if (vec && e.out_dtype == BF16 && (e.kind == EPI_SWIGLU_BWD || e.kind == EPI_GELU_BWD) &&
