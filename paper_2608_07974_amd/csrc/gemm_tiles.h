@@ -1318,13 +1318,20 @@ hipError_t run_layout(const GemmDesc& g, const EpiArgs& e, hipStream_t s, const 
         err = run_dma_split<256, 256, GEMM_WM, GEMM_WN, BKL, NSTL, AK, BKM>(g, e, plan.large ? plan.nz : 1, s);
         which = 3;
       } else {
-        // 64-column wave tiles, or 128-column ones for heads of 128
+        // 64-column wave tiles, or 128-column ones for heads of 128.  Up to 256
+        // blocks have a CU each: 128 KB of stages keep 256 of K in flight, so a
+        // k tile waits an eighth (BK 32) or a quarter (BK 64) of a memory round
+        // trip.  More blocks share a CU with fewer stages each.
+        const long blocks = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * plan.nz;
+        constexpr int NSTD = 256 / BKL;
         bool wide = false;
         if constexpr (AK) {
           wide = heads && e.hd > 64;
           if (wide) err = run_dma_split<128, 128, 4, 1, BKL, NSTL, AK, BKM>(g, e, plan.nz, s);
         }
-        if (!wide) err = run_dma_split<128, 128, 2, 2, BKL, NSTL, AK, BKM>(g, e, plan.nz, s);
+        if (wide) {}
+        else if (blocks <= 256) err = run_dma_split<128, 128, 2, 2, BKL, NSTD, AK, BKM>(g, e, plan.nz, s);
+        else err = run_dma_split<128, 128, 2, 2, BKL, NSTL, AK, BKM>(g, e, plan.nz, s);
         which = 4;
       }
     } else if (large) {
