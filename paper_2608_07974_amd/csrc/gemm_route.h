@@ -1,0 +1,137 @@
+// Which kernel a bf16 GEMM takes: tile, splits of K and copy path, from its
+// sizes alone.  Host arithmetic without HIP, so that it can be checked on the
+// CPU.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+namespace zl {
+
+// What the choice depends on.  may_split: the epilogue allows a split and
+// there is a workspace of part_elems floats.  heads: the RoPE or delta
+// epilogue over heads of hd columns.
+struct GemmShape {
+  int M, N, K;
+  bool ak, bk;  // A, B K-major
+  bool may_split;
+  size_t part_elems;
+  bool heads;
+  int hd;
+};
+
+// Tile size and splits of K, by an estimate of the launch's time from its
+// sizes alone (microseconds; rates measured on the launches of the GPT-2,
+// Llama-1B and 8B shapes at 128 to 16384 tokens):
+//  - a 256 x 256 tile has a CU for itself and takes 0.027 per unit of K; its
+//    prologue and epilogue about 12;
+//  - a 128 x 128 tile shares its CU with a second one once there are more
+//    than 256: 0.018 - 0.020 per unit of K by layout for 512 of them, 0.011 -
+//    0.0125 up to 256, in proportion between; ends about 8;
+//  - splitting K over nz blocks writes and reads nz fp32 partials (at about
+//    4 TB/s) and adds the launch that sums them (5).
+// Each split keeps 256 of K (four to eight k tiles) and the partials stay
+// within the workspace.  What it replaced - large tiles from 240 up, 128 x 128
+// split to the next multiple above 256 blocks below that - took two waves of
+// blocks where one does (48 tiles x 6 = 288 blocks: 511 us; x 5: one wave),
+// 192 large tiles as 768 small ones, and 256 x 256 tiles always for the RoPE and
+// delta epilogues (3 - 48 blocks).
+struct GemmPlan {
+  bool large;
+  int nz;
+};
+inline GemmPlan plan_gemm(const GemmShape& g) {
+  const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
+  const long t128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+  const double alone = g.ak ? 0.0125 : 0.011;
+  const double two = g.ak && g.bk ? 0.020 : 0.018;
+  const double mn = (double)g.M * g.N;
+  long most = 1;  // splits allowed
+  if (g.may_split) {
+    most = g.K / 256;
+    const long by_ws = (long)((double)g.part_elems / mn);
+    if (most > by_ws) most = by_ws;
+    if (most > 64) most = 64;
+    if (most < 1) most = 1;
+  }
+  GemmPlan best = {true, 1};
+  double tb = 0.;
+  for (int large = 1; large >= 0; --large) {
+    const long t = large ? t256 : t128;
+    for (long nz = 1; nz <= most; ++nz) {
+      // more blocks than two rounds need no further split
+      if (nz > 1 && t * nz > 1024) break;
+      const long b = t * nz;
+      const double k = (double)g.K / nz;
+      double c;
+      if (large) {
+        c = (double)((b + 255) / 256) * k * 0.027 + 12.;
+      } else {
+        const long full = b / 512, rem = b % 512;
+        const double last = rem <= 256 ? alone : alone + (two - alone) * (rem - 256) / 256.;
+        c = k * (full * two + (rem == 0 ? 0. : last)) + 8.;
+      }
+      if (nz > 1) c += 5. + nz * mn * 8. / 4e6;
+      if (tb == 0. || c < tb) {
+        tb = c;
+        best = {large != 0, (int)nz};
+      }
+    }
+  }
+  return best;
+}
+
+// K per split, a multiple of the k tile, so every split but the last is
+// whole; returns the number of splits.
+inline int split_k(int K, int nz, int bk, int& ksplit) {
+  ksplit = ((K + nz - 1) / nz + bk - 1) / bk * bk;
+  if (nz <= 1 || ksplit >= K) { ksplit = K; return 1; }
+  return (K + ksplit - 1) / ksplit;
+}
+
+// The direct-to-LDS path copies whole 16-byte chunks with 32-bit buffer
+// offsets from the tile origin: every chunk it reads must be either fully
+// valid or fully outside (K-major: valid k a multiple of 8; MN-major: the
+// M or N extent a multiple of 8), rows 16-byte aligned, and the largest
+// offset below 2^31.
+inline bool dma_operand_ok(const void* p, int64_t ld, bool kmaj, int rows, int kvalid, int R) {
+  if (reinterpret_cast<uintptr_t>(p) % 16 != 0 || ld % 8 != 0) return false;
+  const int64_t lim = (int64_t)1 << 31;
+  if (kmaj) return kvalid % 8 == 0 && ((int64_t)R * ld + kvalid + 64) * 2 < lim;
+  return rows % 8 == 0 && ((int64_t)(kvalid + 64) * ld + R) * 2 < lim;
+}
+
+enum GemmTile {
+  TILE_256,       // 256 x 256, 128-column wave tiles
+  TILE_128,       // 128 x 128, 64-column wave tiles
+  TILE_128_WIDE,  // 128 x 128, 128-column wave tiles (direct-to-LDS, A K-major)
+};
+inline int wave_columns(GemmTile t) { return t == TILE_128 ? 64 : 128; }
+
+struct GemmRoute {
+  GemmTile tile;
+  bool dma;  // direct-to-LDS copies, else the register-staged kernel
+  int nz;    // splits of K (of the direct-to-LDS kernels)
+};
+
+// dma_ok(R): the direct-to-LDS path can copy every operand in tiles of R rows.
+// The RoPE and delta epilogues work on whole heads inside a wave tile: heads of
+// 128 need 128 columns, which the register-staged kernel has in its large tile
+// only.
+template <typename F>
+GemmRoute route_gemm(const GemmShape& g, F&& dma_ok) {
+  const GemmPlan plan = plan_gemm(g);
+  GemmRoute r = {plan.large ? TILE_256 : TILE_128, false, plan.nz};
+  if (g.heads && !plan.large) {
+    if (!g.ak) r = {TILE_256, false, 1};
+    else if (g.hd > 64) r.tile = TILE_128_WIDE;
+  }
+  r.dma = dma_ok(r.tile == TILE_256 ? 256 : 128);
+  if (!r.dma) {
+    if (r.tile == TILE_128_WIDE) r.tile = TILE_256;
+    r.nz = 1;
+  }
+  return r;
+}
+
+}  // namespace zl

@@ -14,6 +14,7 @@
 #include <cstring>
 
 #include "gemm_epilogue.h"
+#include "gemm_route.h"
 
 #ifndef GEMM_IL  // main-loop schedule of the direct-to-LDS kernel
 #define GEMM_IL 2
@@ -1197,80 +1198,10 @@ static hipError_t run_dma(const GemmDesc& g, const EpiArgs& e, hipStream_t s, in
   return hipGetLastError();
 }
 
-// Tile size and splits of K, by an estimate of the launch's time from its
-// sizes alone (microseconds; rates measured on the launches of the GPT-2,
-// Llama-1B and 8B shapes at 128 to 16384 tokens):
-//  - a 256 x 256 tile has a CU for itself and takes 0.027 per unit of K; its
-//    prologue and epilogue about 12;
-//  - a 128 x 128 tile shares its CU with a second one once there are more
-//    than 256: 0.018 - 0.020 per unit of K by layout for 512 of them, 0.011 -
-//    0.0125 up to 256, in proportion between; ends about 8;
-//  - splitting K over nz blocks writes and reads nz fp32 partials (at about
-//    4 TB/s) and adds the launch that sums them (5).
-// Each split keeps 256 of K (four to eight k tiles) and the partials stay
-// within the workspace.  What it replaced - large tiles from 240 up, 128 x 128
-// split to the next multiple above 256 blocks below that - took two waves of
-// blocks where one does (48 tiles x 6 = 288 blocks: 511 us; x 5: one wave),
-// 192 large tiles as 768 small ones, and 256 x 256 tiles always for the RoPE and
-// delta epilogues (3 - 48 blocks).
-struct GemmPlan {
-  bool large;
-  int nz;
-};
-template <bool AK, bool BKM>
-static GemmPlan plan_gemm(const GemmDesc& g, const EpiArgs& e) {
-  const long t256 = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  const long t128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
-  constexpr double alone = AK ? 0.0125 : 0.011;
-  constexpr double two = AK && BKM ? 0.020 : 0.018;
-  const double mn = (double)g.M * g.N;
-  long most = 1;  // splits allowed
-  if (g.part && e.kind != EPI_LOGITS) {
-    most = g.K / 256;
-    const long by_ws = (long)((double)g.part_elems / mn);
-    if (most > by_ws) most = by_ws;
-    if (most > 64) most = 64;
-    if (most < 1) most = 1;
-  }
-  GemmPlan best = {true, 1};
-  double tb = 0.;
-  for (int large = 1; large >= 0; --large) {
-    const long t = large ? t256 : t128;
-    for (long nz = 1; nz <= most; ++nz) {
-      // more blocks than two rounds need no further split
-      if (nz > 1 && t * nz > 1024) break;
-      const long b = t * nz;
-      const double k = (double)g.K / nz;
-      double c;
-      if (large) {
-        c = (double)((b + 255) / 256) * k * 0.027 + 12.;
-      } else {
-        const long full = b / 512, rem = b % 512;
-        const double last = rem <= 256 ? alone : alone + (two - alone) * (rem - 256) / 256.;
-        c = k * (full * two + (rem == 0 ? 0. : last)) + 8.;
-      }
-      if (nz > 1) c += 5. + nz * mn * 8. / 4e6;
-      if (tb == 0. || c < tb) {
-        tb = c;
-        best = {large != 0, (int)nz};
-      }
-    }
-  }
-  return best;
-}
-
-// K per split, a multiple of the k tile, so every split but the last is
-// whole; returns the number of splits.
-static int split_k(GemmDesc& g, int nz, int bk) {
-  g.ksplit = ((g.K + nz - 1) / nz + bk - 1) / bk * bk;
-  if (nz <= 1 || g.ksplit >= g.K) { g.ksplit = g.K; return 1; }
-  return (g.K + g.ksplit - 1) / g.ksplit;
-}
-
 template <int BM, int BN, int WM, int WN, int BK, int NST, bool AK, bool BKM>
 static hipError_t run_dma_split(const GemmDesc& g, const EpiArgs& e, int nz, hipStream_t s) {
   GemmDesc gs = g;
-  nz = split_k(gs, nz, BK);
+  nz = split_k(g.K, nz, BK, gs.ksplit);
   if (nz == 1) return run_dma<BM, BN, WM, WN, BK, NST, AK, BKM>(gs, e, s, 1);
   EpiArgs ep;
   memset(&ep, 0, sizeof(ep));
@@ -1284,70 +1215,47 @@ static hipError_t run_dma_split(const GemmDesc& g, const EpiArgs& e, int nz, hip
   return err == hipSuccess ? launch_splitk_reduce(g.part, nz, g.M, g.N, e, s) : err;
 }
 
-// The direct-to-LDS path copies whole 16-byte chunks with 32-bit buffer
-// offsets from the tile origin: every chunk it reads must be either fully
-// valid or fully outside (K-major: valid k a multiple of 8; MN-major: the
-// M or N extent a multiple of 8), rows 16-byte aligned, and the largest
-// offset below 2^31.
-static bool dma_operand_ok(const void* p, int64_t ld, bool kmaj, int rows, int kvalid, int R) {
-  if (reinterpret_cast<uintptr_t>(p) % 16 != 0 || ld % 8 != 0) return false;
-  const int64_t lim = (int64_t)1 << 31;
-  if (kmaj) return kvalid % 8 == 0 && ((int64_t)R * ld + kvalid + 64) * 2 < lim;
-  return rows % 8 == 0 && ((int64_t)(kvalid + 64) * ld + R) * 2 < lim;
-}
-
 template <bool AK, bool BKM>
 hipError_t run_layout(const GemmDesc& g, const EpiArgs& e, hipStream_t s, const char** kname) {
-  static const char* names[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  static char buf[5][40];
-  int which;
+  const bool heads = e.kind == EPI_ROPE || e.kind == EPI_STORE_DELTA;
+  const GemmShape sh = {g.M, g.N, g.K, AK, BKM, g.part && e.kind != EPI_LOGITS, g.part_elems, heads, e.hd};
+  const GemmRoute r = route_gemm(sh, [&](int R) {
+    return dma_operand_ok(g.A, g.lda, AK, g.M, g.ka, R) && dma_operand_ok(g.B, g.ldb, BKM, g.N, g.kb, R) &&
+           (g.K2 <= 0 || (dma_operand_ok(g.A2, g.lda2, AK, g.M, g.K2, R) &&
+                          dma_operand_ok(g.B2, g.ldb2, BKM, g.N, g.K2, R)));
+  });
+  constexpr int BKL = KTile<AK, BKM>::BK, NSTL = KTile<AK, BKM>::NST;
+  // 64-column wave tiles: up to 256 blocks have a CU each, and 128 KB of stages
+  // keep 256 of K in flight, so a k tile waits an eighth (BK 32) or a quarter
+  // (BK 64) of a memory round trip (1024 x 2048 x 2048, K-major: 34 -> 27 us).
+  // More blocks share a CU with fewer stages each.  The 128-column wave tiles
+  // keep the fewer stages at any count.
+  constexpr int NSTD = 256 / BKL;
+  const long blocks = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * r.nz;
+  const bool large = r.tile == TILE_256;
   hipError_t err;
-  {
-    const GemmPlan plan = plan_gemm<AK, BKM>(g, e);
-    // the RoPE and delta epilogues need wave tiles that hold whole heads
-    const bool heads = e.kind == EPI_ROPE || e.kind == EPI_STORE_DELTA;
-    bool large = plan.large || (heads && !AK);
-    const int R = large ? 256 : 128;
-    const bool dma = dma_operand_ok(g.A, g.lda, AK, g.M, g.ka, R) &&
-                     dma_operand_ok(g.B, g.ldb, BKM, g.N, g.kb, R) &&
-                     (g.K2 <= 0 || (dma_operand_ok(g.A2, g.lda2, AK, g.M, g.K2, R) &&
-                                    dma_operand_ok(g.B2, g.ldb2, BKM, g.N, g.K2, R)));
-    if (dma) {
-      constexpr int BKL = KTile<AK, BKM>::BK, NSTL = KTile<AK, BKM>::NST;
-      if (large) {
-        err = run_dma_split<256, 256, GEMM_WM, GEMM_WN, BKL, NSTL, AK, BKM>(g, e, plan.large ? plan.nz : 1, s);
-        which = 3;
-      } else {
-        // 64-column wave tiles, or 128-column ones for heads of 128.  Up to 256
-        // blocks have a CU each: 128 KB of stages keep 256 of K in flight, so a
-        // k tile waits an eighth (BK 32) or a quarter (BK 64) of a memory round
-        // trip (1024 x 2048 x 2048, K-major: 34 -> 27 us).  More blocks share a CU
-        // with fewer stages each.
-        const long blocks = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * plan.nz;
-        constexpr int NSTD = 256 / BKL;
-        bool wide = false;
-        if constexpr (AK) {
-          wide = heads && e.hd > 64;
-          if (wide) err = run_dma_split<128, 128, 4, 1, BKL, NSTL, AK, BKM>(g, e, plan.nz, s);
-        }
-        if (wide) {}
-        else if (blocks <= 256) err = run_dma_split<128, 128, 2, 2, BKL, NSTD, AK, BKM>(g, e, plan.nz, s);
-        else err = run_dma_split<128, 128, 2, 2, BKL, NSTL, AK, BKM>(g, e, plan.nz, s);
-        which = 4;
-      }
-    } else if (large) {
-      if constexpr (AK && BKM) err = run_mfma<256, 256, 4, 2, AK, BKM>(g, e, s);
-      else err = run_mfma<256, 256, 2, 2, AK, BKM>(g, e, s);
-      which = 1;
-    } else {
-      err = run_mfma<128, 128, 2, 2, AK, BKM>(g, e, s);
-      which = 2;
-    }
+  if (!r.dma && large) {
+    if constexpr (AK && BKM) err = run_mfma<256, 256, 4, 2, AK, BKM>(g, e, s);
+    else err = run_mfma<256, 256, 2, 2, AK, BKM>(g, e, s);
+  } else if (!r.dma) {
+    err = run_mfma<128, 128, 2, 2, AK, BKM>(g, e, s);
+  } else if (large) {
+    err = run_dma_split<256, 256, GEMM_WM, GEMM_WN, BKL, NSTL, AK, BKM>(g, e, r.nz, s);
+  } else if (r.tile == TILE_128_WIDE) {
+    if constexpr (AK) err = run_dma_split<128, 128, 4, 1, BKL, NSTL, AK, BKM>(g, e, r.nz, s);
+    else err = hipErrorInvalidValue;  // route_gemm takes it for a K-major A only
+  } else if (blocks <= 256) {
+    err = run_dma_split<128, 128, 2, 2, BKL, NSTD, AK, BKM>(g, e, r.nz, s);
+  } else {
+    err = run_dma_split<128, 128, 2, 2, BKL, NSTL, AK, BKM>(g, e, r.nz, s);
   }
   if (kname) {
+    static const char* base[4] = {"gemm_mfma_128x128", "gemm_mfma_256x256", "gemm_dma_128x128",
+                                  "gemm_dma_256x256"};
+    static const char* names[4] = {nullptr, nullptr, nullptr, nullptr};
+    static char buf[4][40];
+    const int which = 2 * r.dma + large;
     if (!names[which]) {
-      static const char* base[5] = {"", "gemm_mfma_256x256", "gemm_mfma_128x128",
-                                    "gemm_dma_256x256", "gemm_dma_128x128"};
       snprintf(buf[which], sizeof(buf[which]), "%s_%s", base[which], layout_tag(AK, BKM));
       names[which] = buf[which];
     }

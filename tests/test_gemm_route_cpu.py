@@ -1,0 +1,35 @@
+"""Which kernel a bf16 GEMM takes, by its sizes (host code, no GPU)."""
+import itertools
+
+import pytest
+
+from tests.gemm_route import SPK, TILE_128, TILE_256, route
+
+
+@pytest.mark.parametrize("hd", [16, 32, 64, 128])
+def test_rope_and_delta_tiles_hold_whole_heads(hd):
+    """The RoPE and delta epilogues read a head's columns from one wave tile:
+    its width is a multiple of the head size for every size, layout and copy
+    path, the register-staged kernel's (operands the direct copies cannot
+    reach) among them."""
+    for M, heads, K in itertools.product((1, 100, 128, 600, 2100, 16384), (1, 8, 48, 1024), (64, 2048, 8192)):
+        for ak, bk, d256, d128, part in itertools.product((0, 1), (0, 1), (0, 1), (0, 1), (0, SPK)):
+            r = route(M, heads * hd, K, ak, bk, part, part > 0, True, hd, d256, d128)
+            assert r["wave_cols"] % hd == 0, (M, heads, K, ak, bk, d256, d128, r)
+            assert r["dma"] or r["nz"] == 1
+            assert r["dma"] <= (d256 if r["tile"] == TILE_256 else d128)
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_splits_cover_k_within_the_workspace(ak, bk):
+    """Every split but the last is ksplit deep, the last is not empty, ksplit is
+    a whole number of k tiles, and the partials fit."""
+    bkt = 64 if ak and bk else 32
+    for M, N, K, part in itertools.product((8, 200, 1000, 4096), (72, 768, 3072), (8, 520, 3000, 14336, 128256),
+                                           (0, 5000, SPK)):
+        r = route(M, N, K, ak, bk, part, part > 0)
+        assert r["nz"] >= 1 and (r["nz"] - 1) * r["ksplit"] < K <= r["nz"] * r["ksplit"]
+        if r["nz"] > 1:
+            assert r["ksplit"] % bkt == 0 and r["nz"] * M * N <= part
+    assert route(8192, 8192, 4096, ak, bk)["tile"] == TILE_256
+    assert route(128, 128, 256, ak, bk, 0, False)["tile"] == TILE_128
