@@ -99,20 +99,18 @@ def cpu_baseline(shp, alpha):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2608_07974_amd", "csrc", "gemm_tiles.h")
 
 
-def measured_traffic(kernel, workload):
+def measured_traffic(kernel, workload, record=TRAFFIC_FILE, sources=None):
     """HBM bytes per launch of `kernel` from the committed counter runs
     (FETCH_SIZE + WRITE_SIZE, scaled by a plain-copy calibration), or None if
-    none were taken for this kernel and workload or its source has changed
-    since."""
-    import hashlib
+    none were taken for this kernel and workload or one of the files that
+    define what it reads and writes has changed since."""
+    from paper_2608_07974_amd.profile_summary import GEMM_SOURCES, sources_sha256
     try:
-        with open(TRAFFIC_FILE) as f:
+        with open(record) as f:
             rec = json.load(f)
-        with open(GEMM_SOURCE, "rb") as f:
-            sha = hashlib.sha256(f.read()).hexdigest()
+        sha = sources_sha256(sources or GEMM_SOURCES)
     except OSError:
         return None
     for r in rec.get("kernels", []):

@@ -21,12 +21,30 @@ HBM traffic record (four counter CSVs: FETCH_SIZE and WRITE_SIZE over the
 workload and over the 1 GiB copy calibration):
     python -m paper_2608_07974_amd.profile_summary --traffic-record OUT.json \
         --fetch BENCH.csv COPY.csv --write BENCH.csv COPY.csv \
-        --kernel SUBSTR --name NAME --workload W --source FILE
+        --kernel SUBSTR --name NAME --workload W [--source FILE ...]
 writes the per-launch bytes (each counter scaled by true copy bytes over
-what it read for the copy) with the sha256 of the kernel's source file.
+what it read for the copy) with one sha256 over the kernel's source files.
 """
 import argparse
+import os
 import sqlite3
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
+# What a bf16 GEMM launch reads and writes: main loop, epilogue, operand
+# descriptors, choice of the tile, and the dispatch with the split sum.
+GEMM_SOURCES = [os.path.join(CSRC, f) for f in ("gemm_tiles.h", "gemm_epilogue.h", "gemm_route.h", "common.h",
+                                                "gemm.hip")]
+
+
+def sources_sha256(paths):
+    """One sha256 over the files, each preceded by its name and length."""
+    import hashlib
+    h = hashlib.sha256()
+    for p in paths:
+        with open(p, "rb") as f:
+            data = f.read()
+        h.update(f"{os.path.basename(p)} {len(data)}\n".encode() + data)
+    return h.hexdigest()
 
 
 def summarise(db_path, top=20):
@@ -65,8 +83,7 @@ def pmc_means(csv_path, kernel):
     return {c: (len(d), sum(d.values()) / len(d)) for c, d in per.items() if d}
 
 
-def traffic_record(fetch, write, kernel, name, workload, source, copy_bytes=1 << 30):
-    import hashlib
+def traffic_record(fetch, write, kernel, name, workload, sources, copy_bytes=1 << 30):
     ff = pmc_means(fetch[0], kernel)["FETCH_SIZE"]
     fw = pmc_means(write[0], kernel)["WRITE_SIZE"]
     cf = pmc_means(fetch[1], "copyBuffer")["FETCH_SIZE"][1]
@@ -79,9 +96,7 @@ def traffic_record(fetch, write, kernel, name, workload, source, copy_bytes=1 <<
             if kernel in r["Kernel_Name"]:
                 full = r["Kernel_Name"].split("(zl::")[0].replace("void ", "")
                 break
-    with open(source, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
-    return {"kernel": name, "workload": workload, "rocprof_kernel": full, "source_sha256": sha,
+    return {"kernel": name, "workload": workload, "rocprof_kernel": full, "source_sha256": sources_sha256(sources),
             "dispatches": ff[0], "fetch_kib_per_dispatch": ff[1], "write_kib_per_dispatch": fw[1],
             "copy_factor_fetch": round(kf, 5), "copy_factor_write": round(kw, 5),
             "hbm_bytes_per_launch": int(round((ff[1] * kf + fw[1] * kw) * 1024))}
@@ -181,7 +196,7 @@ if __name__ == "__main__":
     ap.add_argument("--write", nargs=2, default=None)
     ap.add_argument("--name", default="")
     ap.add_argument("--workload", default="")
-    ap.add_argument("--source", default="")
+    ap.add_argument("--source", nargs="+", default=GEMM_SOURCES)
     ap.add_argument("--report", default=None,
                     help="counter report: kernel-trace CSV, then --pmc-csvs and --copy")
     ap.add_argument("--pmc-csvs", nargs="+", default=[])
