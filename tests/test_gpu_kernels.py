@@ -379,3 +379,41 @@ def test_lora_factor_gradients(arch, rank, B, S):
                 assert float((got - ref).norm() / ref.norm()) < 1e-3, key
             col += w
     ch.close()
+
+
+@pytest.mark.parametrize("arch", ["llama", "gpt2"])
+@pytest.mark.parametrize("T", [4104, 8216, 16400, 40000])
+def test_norm_and_bias_gradients_of_many_rows(arch, T):
+    """Column sums over 512 partial rows (one stage of the reduction), 513 and
+    1025 (two stages, the last group one row) and 2048 (blocks without rows
+    among them): the norm gradients, and with a LayerNorm the bias
+    gradients taken from the norm backward, against fp64 sums of the chunk's
+    own operands.  Bound: each sum is at most 20 rows in a block, then trees,
+    with a few roundings per term: under 64 units of fp32 of the absolute sum."""
+    import workload
+    from paper_2608_07974_amd.chunk import TorchChunk, config_from_shape
+    zl = _zl()
+    shp = workload.get_config("tiny").with_(arch=arch, d_ff=64, vocab=64, batch=T // 8, seq=8)
+    ch = TorchChunk(config_from_shape(shp, alpha=1.0, optimizer="sgd"))
+    gen = torch.Generator(device=_dev()).manual_seed(T)
+    ch.master.normal_(0.0, 0.1, generator=gen)
+    ch.head_w.normal_(0.0, 0.1, generator=gen)
+    zl.zl_refresh_shadow(ch.handle, _stream())
+    h = torch.randn(T // 8, 8, 64, device=_dev(), generator=gen)
+    ch.forward(h)
+    ch.objective(torch.randint(0, 64, (T // 8, 8), device=_dev(), generator=gen).to(torch.int32))
+    ch.backward(1.0, 0)
+    x, dn = ch.inspect_device("x", 0).double(), ch.inspect_device("dn").double()
+    if arch == "gpt2":
+        x = x - x.mean(1, keepdim=True)
+    xhat = x * ch.inspect_device("rstd1", 0).double()
+    want = {"L0.ln1_w": dn * xhat}
+    if arch == "gpt2":
+        want.update({"L0.ln1_b": dn, "L0.bo": ch.inspect_device("dxb").double(),
+                     "L0.bproj": ch.inspect_device("dxa").double()})
+    for key, terms in want.items():
+        got = ch.view(ch.grad, key).double().reshape(-1)
+        size = terms.abs().sum(0)
+        assert bool((size > 0).all()), key
+        assert bool(((got - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * size).all()), key
+    ch.close()
