@@ -8,6 +8,7 @@
 // under the current one's products), and the four waves take a quarter of the
 // k tile each, their sums meeting in LDS in wave order.
 #include "gemm_epilogue.h"
+#include "gemm_route.h"
 
 namespace zl {
 
@@ -129,17 +130,78 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmDesc g, EpiArgs e) {
   for (int i = 0; i < 4; ++i) epilogue(e, g.M, g.N, m0 + row, n0 + col + i, s[i]);
 }
 
-hipError_t launch_gemm_f32(const GemmDesc& g, const EpiArgs& e, hipStream_t s) {
-  const dim3 grid(((g.N + FT - 1) / FT) * ((g.M + FT - 1) / FT));
-  if (g.a_kmajor && g.b_kmajor)
-    hipLaunchKernelGGL((gemm_f32_kernel<true, true>), grid, dim3(256), 0, s, g, e);
-  else if (g.a_kmajor)
-    hipLaunchKernelGGL((gemm_f32_kernel<true, false>), grid, dim3(256), 0, s, g, e);
-  else if (g.b_kmajor)
-    hipLaunchKernelGGL((gemm_f32_kernel<false, true>), grid, dim3(256), 0, s, g, e);
-  else
-    hipLaunchKernelGGL((gemm_f32_kernel<false, false>), grid, dim3(256), 0, s, g, e);
+// The same product on the vector ALUs: one 64 x 64 output tile per block, 4 x 4
+// per thread, 16 of K a step.  It moves half the operand bytes per product of
+// the 32 x 32 tiles and wins once the launch fills the chip.
+template <bool AK, bool BKM>
+__global__ void __launch_bounds__(256) gemm_simt_kernel(GemmDesc g, EpiArgs e) {
+  constexpr int BM = 64, BN = 64, BK = 16;
+  __shared__ float As[BK][BM + 4];
+  __shared__ float Bs[BK][BN + 4];
+  const int nbn = (g.N + BN - 1) / BN;
+  const int m0 = blockIdx.x / nbn * BM, n0 = blockIdx.x % nbn * BN;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  float acc[4][4] = {};
+  // segment 0: (A, B) over K; segment 1: (A2, B2) over K2
+  for (int seg = 0; seg < 2; ++seg) {
+    const float* A = reinterpret_cast<const float*>(seg ? g.A2 : g.A);
+    const float* B = reinterpret_cast<const float*>(seg ? g.B2 : g.B);
+    const int64_t lda = seg ? g.lda2 : g.lda, ldb = seg ? g.ldb2 : g.ldb;
+    const int K = seg ? g.K2 : g.K, ka = seg ? g.K2 : g.ka, kb = seg ? g.K2 : g.kb;
+    for (int k0 = 0; k0 < K; k0 += BK) {
+      for (int idx = threadIdx.x; idx < BM * BK; idx += 256) {
+        int r, k;
+        if (AK) { r = idx / BK; k = idx % BK; } else { r = idx % BM; k = idx / BM; }
+        const int gr = m0 + r, gk = k0 + k;
+        float v = 0.f;
+        if (gr < g.M && gk < ka) v = AK ? A[(int64_t)gr * lda + gk] : A[(int64_t)gk * lda + gr];
+        As[k][r] = v;
+      }
+      for (int idx = threadIdx.x; idx < BN * BK; idx += 256) {
+        int r, k;
+        if (BKM) { r = idx / BK; k = idx % BK; } else { r = idx % BN; k = idx / BN; }
+        const int gr = n0 + r, gk = k0 + k;
+        float v = 0.f;
+        if (gr < g.N && gk < kb) v = BKM ? B[(int64_t)gr * ldb + gk] : B[(int64_t)gk * ldb + gr];
+        Bs[k][r] = v;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < BK; ++k) {
+        float a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+      }
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) epilogue(e, g.M, g.N, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j]);
+}
+
+template <bool AK, bool BKM>
+static hipError_t run_f32(const GemmDesc& g, const EpiArgs& e, hipStream_t s) {
+  if (f32_large_tiles(g.M, g.N, g.K + g.K2, AK, BKM)) {
+    const dim3 grid(((g.N + 63) / 64) * ((g.M + 63) / 64));
+    hipLaunchKernelGGL((gemm_simt_kernel<AK, BKM>), grid, dim3(256), 0, s, g, e);
+  } else {
+    const dim3 grid(((g.N + FT - 1) / FT) * ((g.M + FT - 1) / FT));
+    hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM>), grid, dim3(256), 0, s, g, e);
+  }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32(const GemmDesc& g, const EpiArgs& e, hipStream_t s) {
+  if (g.a_kmajor) return g.b_kmajor ? run_f32<true, true>(g, e, s) : run_f32<true, false>(g, e, s);
+  return g.b_kmajor ? run_f32<false, true>(g, e, s) : run_f32<false, false>(g, e, s);
 }
 
 }  // namespace zl

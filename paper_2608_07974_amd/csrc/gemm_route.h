@@ -134,4 +134,18 @@ GemmRoute route_gemm(const GemmShape& g, F&& dma_ok) {
   return r;
 }
 
+// fp32 GEMMs: 64 x 64 tiles on the vector ALUs, else 32 x 32 tiles on fp32 MFMA.
+// The small tiles fill the chip and load 128 of K per round trip; the large ones
+// read each operand half as often and do not pad K to 128, and win from this
+// many tiles up (4096 x 4096 x 2048, both K-major: 1117 us against 2012; at
+// 1024 x 768 x 2048: 317 against 107; crossings measured at K 8 to 1024).  Both
+// operands MN-major the small tiles load without a transpose and win at any
+// count where K fills its tiles (4096 x 4096 x 2048: 1041 against 809).
+inline bool f32_large_tiles(int M, int N, int K, bool ak, bool bk) {
+  const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64);
+  const double fill = K > 0 ? K / (double)((K + 127) / 128 * 128) : 1.;
+  if (!ak && !bk) return fill < 0.8 && tiles > 1500. * fill;
+  return tiles > (ak && bk ? 500. : 800.) * fill;
+}
+
 }  // namespace zl

@@ -23,6 +23,9 @@ extern "C" void route(int M, int N, int K, int ak, int bk, int may_split, size_t
   out[2] = zl::split_k(K, r.nz, bkt, out[4]);
   out[3] = zl::wave_columns(r.tile);
 }
+extern "C" int f32_large(int M, int N, int K, int ak, int bk) {
+  return zl::f32_large_tiles(M, N, K, ak != 0, bk != 0);
+}
 """
 
 
@@ -43,3 +46,8 @@ def route(M, N, K, ak, bk, part_elems=SPK, may_split=True, heads=False, hd=0, dm
     _lib().route(M, N, K, int(ak), int(bk), int(may_split), ctypes.c_size_t(part_elems), int(heads), hd,
                  int(dma256), int(dma128), 64 if ak and bk else 32, out)
     return dict(tile=out[0], dma=bool(out[1]), nz=out[2], wave_cols=out[3], ksplit=out[4])
+
+
+def f32_large(M, N, K, ak, bk):
+    """Whether an fp32 GEMM takes the 64 x 64 tiles."""
+    return bool(_lib().f32_large(M, N, K, int(ak), int(bk)))

@@ -381,6 +381,29 @@ def test_lora_factor_gradients(arch, rank, B, S):
     ch.close()
 
 
+@pytest.mark.parametrize("M,N,K,K2", [(2050, 1030, 24, 0), (1000, 3000, 5, 16), (1536, 4200, 40, 0), (777, 1100, 129, 0)])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn"])
+def test_gemm_f32_tiles(layout, M, N, K, K2):
+    """fp32 products of many tiles: the 64 x 64 tiles (short K, a second
+    segment, rows and columns past the last tile) and, the last shape, the
+    32 x 32 ones with one k past a tile of 128."""
+    from tests.gemm_route import f32_large
+    zl = _zl()
+    rng = np.random.default_rng(M + N + K)
+    At, Bt, a_k, b_k = _gemm_operands(rng, layout, M, N, K, torch.float32)
+    A2, B2, _, _ = _gemm_operands(rng, layout, M, N, K2, torch.float32)
+    assert f32_large(M, N, K + K2, a_k, b_k) == (K < 100)
+    C = torch.full((M + 1, N), float("nan"), device=_dev())
+    torch.cuda.synchronize()
+    seg = dict(K2=K2, A2=A2.data_ptr(), lda2=A2.shape[1], B2=B2.data_ptr(), ldb2=B2.shape[1]) if K2 else {}
+    zl.zl_kernel_gemm(M, N, K, At.data_ptr(), At.shape[1], a_k, Bt.data_ptr(), Bt.shape[1], b_k, C.data_ptr(), N,
+                      zl.ZL_F32, _stream(), **seg)
+    torch.cuda.synchronize()
+    ref = _gemm_ref(At, Bt, a_k, b_k) + (_gemm_ref(A2, B2, a_k, b_k) if K2 else 0.0)
+    assert bool(torch.isnan(C[M]).all())
+    assert rel_err(C[:M].cpu().double().numpy(), ref) < 2e-6
+
+
 @pytest.mark.parametrize("arch", ["llama", "gpt2"])
 @pytest.mark.parametrize("T", [4104, 8216, 16400, 40000])
 def test_norm_and_bias_gradients_of_many_rows(arch, T):
