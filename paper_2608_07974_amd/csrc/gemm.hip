@@ -1,5 +1,6 @@
 // GEMM dispatch by type and operand layout, and the split-K reduction.
 #include "gemm_epilogue.h"
+#include "gemm_route.h"
 
 namespace zl {
 
@@ -90,13 +91,21 @@ hipError_t launch_gemm_f32(const GemmDesc& g, const EpiArgs& e, hipStream_t s);
 bool skinny_ok(const GemmDesc& g, const EpiArgs& e);
 hipError_t launch_gemm_skinny(const GemmDesc* g, const EpiArgs* e, int np, hipStream_t s);
 
+static GemmShape shape_of(const GemmDesc& g) {
+  return {g.M, g.N, g.K, g.a_kmajor, g.b_kmajor, g.part != nullptr, g.part_elems, false, 0};
+}
+
 bool launch_gemm_group(const GemmDesc* g, const EpiArgs* e, int np, int dtype, hipStream_t s,
                        hipError_t* err) {
   if (dtype != BF16 || np < 1 || np > 3) return false;
-  for (int i = 0; i < np; ++i)
+  GemmShape sh[3];
+  for (int i = 0; i < np; ++i) {
     if (g[i].M <= 0 || g[i].N <= 0 || g[i].M != g[0].M || g[i].b_kmajor != g[0].b_kmajor ||
         !skinny_ok(g[i], e[i]))
       return false;
+    sh[i] = shape_of(g[i]);
+  }
+  if (!skinny_better(sh, np)) return false;
   *err = launch_gemm_skinny(g, e, np, s);
   return true;
 }
@@ -132,7 +141,8 @@ hipError_t launch_gemm(const GemmDesc& g, const EpiArgs& e, int dtype, hipStream
     if (kname) *kname = "gemm_f32_32x32";
     return launch_gemm_f32(g, e, s);
   }
-  if (skinny_ok(g, e)) {
+  const GemmShape sh = shape_of(g);
+  if (skinny_ok(g, e) && skinny_better(&sh, 1)) {
     if (kname) *kname = "gemm_skinny";
     return launch_gemm_skinny(&g, &e, 1, s);
   }

@@ -1011,6 +1011,8 @@ zl_status zl_chunk_backward(zl_chunk* c, float grad_scale, int accumulate, void*
       ee[j].scale = m.ls;
       ge[j] = gdesc(T, r, widths[j], static_cast<const char*>(dy) + (size_t)col * asz, out, true,
                     c->WT(boff), r, false);
+      ge[j].part = p.spk_elems ? c->at<float>(p.SPK) : nullptr;  // what run_gemm would split into
+      ge[j].part_elems = p.spk_elems;
       col += widths[j];
       boff += (size_t)widths[j] * r;
     }

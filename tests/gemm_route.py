@@ -23,6 +23,11 @@ extern "C" void route(int M, int N, int K, int ak, int bk, int may_split, size_t
   out[2] = zl::split_k(K, r.nz, bkt, out[4]);
   out[3] = zl::wave_columns(r.tile);
 }
+extern "C" int skinny(int M, int N, int K, int bk, size_t part_elems, int np) {
+  const zl::GemmShape g = {M, N, K, true, bk != 0, part_elems > 0, part_elems, false, 0};
+  const zl::GemmShape p[3] = {g, g, g};
+  return zl::skinny_better(p, np);
+}
 extern "C" int f32_large(int M, int N, int K, int ak, int bk) {
   return zl::f32_large_tiles(M, N, K, ak != 0, bk != 0);
 }
@@ -51,3 +56,8 @@ def route(M, N, K, ak, bk, part_elems=SPK, may_split=True, heads=False, hd=0, dm
 def f32_large(M, N, K, ak, bk):
     """Whether an fp32 GEMM takes the 64 x 64 tiles."""
     return bool(_lib().f32_large(M, N, K, int(ak), int(bk)))
+
+
+def skinny(M, N, K, bk, part_elems=SPK, np=1):
+    """Whether np products of few columns over a K-major A take whole rows per block."""
+    return bool(_lib().skinny(M, N, K, int(bk), ctypes.c_size_t(part_elems), np))

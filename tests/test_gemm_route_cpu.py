@@ -3,7 +3,7 @@ import itertools
 
 import pytest
 
-from tests.gemm_route import SPK, TILE_128, TILE_256, f32_large, route
+from tests.gemm_route import SPK, TILE_128, TILE_256, f32_large, route, skinny
 
 
 @pytest.mark.parametrize("hd", [16, 32, 64, 128])
@@ -46,3 +46,22 @@ def test_fp32_tiles_by_size():
         for M, N, K in ((128, 256, 64), (256, 256, 8), (512, 512, 1024), (1, 1, 1), (64, 64, 0)):
             assert not f32_large(M, N, K, ak, bk), (M, N, K)
     assert not f32_large(8192, 8192, 2048, 0, 0)
+
+
+@pytest.mark.parametrize("M,N,K,bk,part,rows", [
+    (8, 8, 64, 1, 0, True), (1024, 8, 2048, 1, SPK, True), (4096, 16, 4096, 1, SPK, True), (8192, 8, 2048, 0, SPK, True),
+    (2048, 64, 14336, 1, 0, True), (8, 8, 65536, 0, 0, True), (32768, 8, 64, 1, SPK, True),
+    # long K that tiles can split, or many rows of 64 columns: two to eight times
+    # slower as whole rows per block
+    (512, 64, 65536, 1, SPK, False), (8, 64, 14336, 1, SPK, False), (200, 32, 14336, 0, SPK, False),
+    (2048, 16, 65536, 0, SPK, False), (8192, 64, 14336, 0, SPK, False), (16384, 64, 4096, 1, 0, False),
+    (16384, 64, 2048, 0, SPK, False)])
+def test_few_columns_by_size(M, N, K, bk, part, rows):
+    """The kernel for few output columns only where it measured faster than tiles."""
+    assert skinny(M, N, K, bk, part) == rows
+
+
+def test_few_columns_of_several_products():
+    """Products that share a launch count once for its latency, and each for its rows."""
+    assert skinny(1024, 8, 8192, 0, SPK, 2) and skinny(1024, 24, 2048, 0, SPK, 3)
+    assert not skinny(16384, 64, 14336, 0, SPK, 2)

@@ -311,25 +311,36 @@ def test_backward_pairs_weight_gradients():
     assert launches == 4
 
 
+@pytest.mark.parametrize("pad", [0, 24])
 @pytest.mark.parametrize("b_k", [True, False])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (16, 16, 128), (17, 24, 1032), (1000, 40, 2048), (300, 64, 136),
                                    (8200, 8, 520), (8200, 32, 264)])
-def test_gemm_few_columns(b_k, M, N, K):
+def test_gemm_few_columns(b_k, M, N, K, pad):
     """At most 64 output columns over a K-major A (the LoRA products): rows
     past a block's 16 or 32, columns past 16 or 32, K past the waves' 128-wide
-    slices, all against fp64 within fp32 summation error."""
+    slices, all against fp64 within fp32 summation error; dense rows, and rows
+    of a wider matrix (as the chunk's, whose operands lie beside each other)
+    whose other columns are neither read into the product nor written."""
+    from tests.gemm_route import skinny
+    assert skinny(M, N, K, b_k, 0)
     zl = _zl()
     gen = torch.Generator(device=_dev()).manual_seed(M + N + K)
-    A = torch.randn(M, K, device=_dev(), generator=gen).to(torch.bfloat16)
-    B = torch.randn(*((N, K) if b_k else (K, N)), device=_dev(), generator=gen).to(torch.bfloat16)
-    C = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device=_dev())
+
+    def op(rows, cols):
+        x = torch.full((rows, cols + pad), float("nan"), device=_dev(), dtype=torch.bfloat16)
+        x[:, :cols] = torch.randn(rows, cols, device=_dev(), generator=gen).to(torch.bfloat16)
+        return x
+    A, B = op(M, K), op(*((N, K) if b_k else (K, N)))
+    C = torch.full((M + 1, N + pad), float("nan"), dtype=torch.float32, device=_dev())
     torch.cuda.synchronize()
-    zl.zl_kernel_gemm(M, N, K, A.data_ptr(), K, True, B.data_ptr(), B.shape[1], b_k, C.data_ptr(), N,
+    zl.zl_kernel_gemm(M, N, K, A.data_ptr(), K + pad, True, B.data_ptr(), B.shape[1], b_k, C.data_ptr(), N + pad,
                       zl.ZL_BF16, _stream())
     torch.cuda.synchronize()
-    ref = A.double().cpu() @ (B.t() if b_k else B).double().cpu()
+    A, B = A[:, :K].double().cpu(), B[:, :K if b_k else N].double().cpu()
+    ref = A @ (B.t() if b_k else B)
     assert bool(torch.isnan(C[M]).all())  # nothing written past the last row
-    assert rel_err(C[:M].cpu().double().numpy(), ref.numpy()) < 2e-6
+    assert bool(torch.isnan(C[:, N:]).all())
+    assert rel_err(C[:M, :N].cpu().double().numpy(), ref.numpy()) < 2e-6
 
 
 @pytest.mark.parametrize("arch,rank,B,S", [("1b", 4, 1, 37), ("1b", 16, 3, 700), ("1b", 24, 2, 65), ("gpt2", 8, 5, 203)])
