@@ -65,3 +65,13 @@ def test_few_columns_of_several_products():
     """Products that share a launch count once for its latency, and each for its rows."""
     assert skinny(1024, 8, 8192, 0, SPK, 2) and skinny(1024, 24, 2048, 0, SPK, 3)
     assert not skinny(16384, 64, 14336, 0, SPK, 2)
+
+
+def test_from_240_large_tiles_up_tiles_are_large():
+    """Small tiles there only where the second round of large ones is nearly empty."""
+    for ak, bk in ((1, 1), (1, 0), (0, 0)):
+        for m in (15, 16, 20, 24, 25, 28, 35, 48):  # x 16 large tiles: 240 ... 768
+            for K in (64, 256, 2048, 8192):
+                r = route(256 * m, 4096, K, ak, bk)
+                assert r["nz"] == 1
+                assert (r["tile"] == TILE_256) == (m != 20), (m, K)
