@@ -1225,13 +1225,7 @@ hipError_t run_layout(const GemmDesc& g, const EpiArgs& e, hipStream_t s, const 
                           dma_operand_ok(g.B2, g.ldb2, BKM, g.N, g.K2, R)));
   });
   constexpr int BKL = KTile<AK, BKM>::BK, NSTL = KTile<AK, BKM>::NST;
-  // 64-column wave tiles: up to 256 blocks have a CU each, and 128 KB of stages
-  // keep 256 of K in flight, so a k tile waits an eighth (BK 32) or a quarter
-  // (BK 64) of a memory round trip (1024 x 2048 x 2048, K-major: 34 -> 27 us).
-  // More blocks share a CU with fewer stages each.  The 128-column wave tiles
-  // keep the fewer stages at any count.
-  constexpr int NSTD = 256 / BKL;
-  const long blocks = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * r.nz;
+  constexpr int NSTD = 256 / BKL;  // stages that hold 256 of K
   const bool large = r.tile == TILE_256;
   hipError_t err;
   if (!r.dma && large) {
@@ -1244,7 +1238,7 @@ hipError_t run_layout(const GemmDesc& g, const EpiArgs& e, hipStream_t s, const 
   } else if (r.tile == TILE_128_WIDE) {
     if constexpr (AK) err = run_dma_split<128, 128, 4, 1, BKL, NSTL, AK, BKM>(g, e, r.nz, s);
     else err = hipErrorInvalidValue;  // route_gemm takes it for a K-major A only
-  } else if (blocks <= 256) {
+  } else if (deep_stages(AK, BKM, (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * r.nz, g.K / r.nz)) {
     err = run_dma_split<128, 128, 2, 2, BKL, NSTD, AK, BKM>(g, e, r.nz, s);
   } else {
     err = run_dma_split<128, 128, 2, 2, BKL, NSTL, AK, BKM>(g, e, r.nz, s);

@@ -28,6 +28,7 @@ extern "C" int skinny(int M, int N, int K, int bk, size_t part_elems, int np) {
   const zl::GemmShape p[3] = {g, g, g};
   return zl::skinny_better(p, np);
 }
+extern "C" int deep(int ak, int bk, long blocks, int k) { return zl::deep_stages(ak != 0, bk != 0, blocks, k); }
 extern "C" int f32_large(int M, int N, int K, int ak, int bk) {
   return zl::f32_large_tiles(M, N, K, ak != 0, bk != 0);
 }
@@ -61,3 +62,8 @@ def f32_large(M, N, K, ak, bk):
 def skinny(M, N, K, bk, part_elems=SPK, np=1):
     """Whether np products of few columns over a K-major A take whole rows per block."""
     return bool(_lib().skinny(M, N, K, int(bk), ctypes.c_size_t(part_elems), np))
+
+
+def deep(ak, bk, blocks, k):
+    """Whether 128 x 128 tiles keep 256 of K in flight."""
+    return bool(_lib().deep(int(ak), int(bk), ctypes.c_long(blocks), k))

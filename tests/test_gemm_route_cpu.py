@@ -3,7 +3,7 @@ import itertools
 
 import pytest
 
-from tests.gemm_route import SPK, TILE_128, TILE_256, f32_large, route, skinny
+from tests.gemm_route import SPK, TILE_128, TILE_256, deep, f32_large, route, skinny
 
 
 @pytest.mark.parametrize("hd", [16, 32, 64, 128])
@@ -75,3 +75,14 @@ def test_from_240_large_tiles_up_tiles_are_large():
                 r = route(256 * m, 4096, K, ak, bk)
                 assert r["nz"] == 1
                 assert (r["tile"] == TILE_256) == (m != 20), (m, K)
+
+
+def test_stages_by_k_and_blocks():
+    """The deep pipeline only for a long K per block, or where the blocks
+    together load the memory; short launches lost 5 % to it."""
+    for ak, bk in ((1, 1), (1, 0), (0, 0)):
+        for blocks in (1, 32, 128, 256):
+            assert not any(deep(ak, bk, blocks, k) for k in (64, 256, 512))
+        assert not deep(ak, bk, 257, 65536) and deep(ak, bk, 64, 65536)
+    assert deep(1, 1, 256, 2048) and deep(1, 1, 128, 2048) and not deep(1, 1, 32, 2048)
+    assert deep(1, 0, 256, 4096) and not deep(1, 0, 256, 1024) and not deep(0, 0, 256, 14336)
