@@ -160,26 +160,28 @@ GemmRoute route_gemm(const GemmShape& g, F&& dma_ok) {
 // Products of few columns (N <= 64, np of them with the same M in one launch):
 // whole rows per block (gemm_skinny.hip) or the tiles above, by estimates of
 // both (microseconds) fitted to launches of 8 - 32768 rows, 8 - 64 columns and K
-// 64 - 65536.  A row block takes 1.4 / 2.1 / 3.4 per 1024 of K at up to 16 / 32 /
-// 64 columns, more in proportion past 256 blocks of 16 rows, and no less than
-// reading A at 5.1 TB/s; tiles can split K where there is a workspace.  The
-// row blocks have to win by 15 %, the estimates' error.  (8192 x 64 x 14336 with
-// a workspace: 126 us against 43 as tiles; 1024 x 8 x 2048: 5 against 13.)
+// 64 - 65536.  A row block takes 1.1 / 1.57 / 2.1 / 3.4 per 1024 of K at up to 8 /
+// 16 / 32 / 64 columns, more in proportion past 256 blocks of 16 rows, and no
+// less than reading A at 5.2 TB/s; tiles can split K where there is a
+// workspace.  Near a tie (5 %) it is tiles, whose estimate is the closer one.
+// (8192 x 64 x 14336 with a workspace: 126 us as rows against 47; 1024 x 8 x 2048:
+// 5 against 13.)
 inline bool skinny_better(const GemmShape* g, int np) {
   double lat = 0., all = 0., bytes = 0., tiles = 0.;
   for (int i = 0; i < np; ++i) {
-    const double per = (g[i].N <= 16 ? 1.4 : g[i].N <= 32 ? 2.1 : 3.4) * (g[i].bk ? 1. : 0.9);
+    const int N = g[i].N;
+    const double per = (N <= 8 ? 1.1 : N <= 16 ? 1.57 : N <= 32 ? 2.1 : 3.4) * (g[i].bk ? 1. : 0.9);
     const double one = g[i].K / 1024. * per;
     if (one > lat) lat = one;
     all += one * 1.15 * ((g[i].M + 15) / 16) / 256.;
-    bytes += (double)g[i].M * g[i].K * 2. / 5.1e6;
+    bytes += (double)g[i].M * g[i].K * 2. / 5.2e6;
     const int nz = plan_gemm(g[i]).nz;
-    const double blocks = (double)((g[i].M + 127) / 128) * ((g[i].N + 127) / 128) * nz;
-    tiles += 8.5 + (double)g[i].K / nz * (0.007 + 0.0045 * blocks / 256.) +
-             (nz > 1 ? nz * (double)g[i].M * g[i].N * 8. / 4.2e6 : 0.);
+    const double blocks = (double)((g[i].M + 127) / 128) * ((N + 127) / 128) * nz;
+    tiles += 8.4 + (double)g[i].K / nz * (0.007 + 0.005 * blocks / 256.) +
+             (nz > 1 ? nz * (0.062 + (double)g[i].M * N * 8. / 5.5e6) : 0.);
   }
   const double rows = 3.2 + (lat > all ? (lat > bytes ? lat : bytes) : (all > bytes ? all : bytes));
-  return rows < 0.85 * tiles;
+  return rows < 0.95 * tiles;
 }
 
 // fp32 GEMMs: 64 x 64 tiles on the vector ALUs, else 32 x 32 tiles on fp32 MFMA.
