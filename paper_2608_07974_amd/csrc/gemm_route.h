@@ -54,12 +54,14 @@ inline GemmPlan plan_gemm(const GemmShape& g) {
     if (most > 64) most = 64;
     if (most < 1) most = 1;
   }
-  // From 240 large tiles up the estimate decides nothing: large tiles, unless
-  // their second round would leave three quarters of the chip idle (measured at
-  // 64 to 6144 of K in the three layouts: small over large is 0.83 - 0.95 at 288
-  // and 320 tiles, but 1.08 - 1.24 at 240 and 256 of K 256, 1.04 - 1.14 at 376 and
-  // 384, 1.03 - 1.15 from 400 up, and 1.05 - 1.10 at 560 of K 8192 - 16384).
-  if (t256 >= 240) return {t256 <= 256 || t256 > 320, 1};
+  // From 240 large tiles up that are not mostly padding (an eighth at most; 80
+  // rows of logits take 117 us as 1002 small tiles, 147 as 501 large ones) the
+  // estimate decides nothing: large tiles, unless their second round would leave
+  // three quarters of the chip idle (measured at 64 to 6144 of K in the three
+  // layouts: small over large is 0.83 - 0.95 at 288 and 320 tiles, but 1.08 - 1.24
+  // at 240 and 256 of K 256, 1.04 - 1.14 at 376 and 384, 1.03 - 1.15 from 400 up,
+  // and 1.05 - 1.10 at 560 of K 8192 - 16384).
+  if (t256 >= 240 && 2 * t128 >= 7 * t256) return {t256 <= 256 || t256 > 320, 1};
   GemmPlan best = {true, 1};
   double tb = 0.;
   for (int large = 1; large >= 0; --large) {

@@ -75,6 +75,7 @@ def test_from_240_large_tiles_up_tiles_are_large():
                 r = route(256 * m, 4096, K, ak, bk)
                 assert r["nz"] == 1
                 assert (r["tile"] == TILE_256) == (m != 20), (m, K)
+        assert route(80, 128256, 2048, ak, bk, 0, False)["tile"] == TILE_128  # half of a large tile is padding
 
 
 def test_stages_by_k_and_blocks():
