@@ -110,20 +110,17 @@ inline bool dma_operand_ok(const void* p, int64_t ld, bool kmaj, int rows, int k
 }
 
 // Whether 128 x 128 tiles of 64-column wave tiles keep 256 of K in flight (128 KB of
-// stages, one block per CU) instead of two or three k tiles (48 - 64 KB).  The
-// deeper pipeline costs about 5 % of a short launch (it starts with eight or
-// four tiles of copies) and pays where a block's K is long or the blocks
-// together load the memory: measured over 64 - 4096 rows, 72 - 4096 columns, K
-// 64 - 14336, deep over shallow is, both operands K-major, 1.05 at K 64, 1.02
-// at K 2048 on 32 blocks, 0.98 on 128, 0.89 on 256, 0.78 at K 14336 on any;
-// one K-major 1.05 to K 1024, 0.97 at K 4096 on 256 blocks, 0.96 at K 14336; none
-// 1.05 to 1.00 up to K 14336, 0.89 at K 65536.
+// stages, one block per CU) instead of two or three k tiles (48 - 64 KB).  Both
+// operands K-major: at any K (all forward GEMMs of a Llama-1B layer at 64 to 512
+// tokens 214 - 325 us against 227 - 343).  With an MN-major operand the eight
+// stages fill with as many copies of 32 k first, which pays where a block's K
+// is long or the blocks together load the memory: data and weight gradients of a
+// GPT-2 layer at 256 tokens 160 and 109 us against 150 and 104 with three
+// stages, at 8192 tokens 522 and 524 against 534 and 571; at 2048 tokens (295000
+// of K over all blocks) both are even.
 inline bool deep_stages(bool ak, bool bk, long blocks, int k) {
   if (blocks > 256) return false;
-  const double all = (double)blocks * k;
-  if (ak && bk) return k >= 4096 || all >= 1 << 18;
-  if (ak || bk) return k >= 8192 || all >= 1 << 20;
-  return k >= 32768;
+  return (ak && bk) || k >= 8192 || (double)blocks * k > 3e5;
 }
 
 enum GemmTile {
