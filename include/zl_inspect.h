@@ -57,7 +57,8 @@ zl_status zl_inspect(const zl_chunk* chunk, const char* name, int layer, zl_view
  * A[k*lda + m] and likewise for B, A2 (lda2) and B2 (ldb2) in the layouts of
  * A and B; the GEMM kernel used for every linear of the chunk (Eq. (1)), the
  * second segment carrying the LoRA term (K2 = 0: none, A2 and B2 unused),
- * and the head (Eq. (2)).  dtype ZL_BF16 (MFMA) or ZL_F32 (SIMT).
+ * and the head (Eq. (2)).  dtype ZL_BF16 (MFMA) or ZL_F32 (fp32 MFMA; the vector
+ * ALUs where the output has many tiles).
  * workspace (device, workspace_elems floats, or NULL): lets a bf16 GEMM
  * whose output has too few tiles to fill the GPU split K into fp32 partials
  * there, summed in a fixed order (the chunk's own GEMMs use a region of its

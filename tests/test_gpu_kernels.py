@@ -451,3 +451,74 @@ def test_norm_and_bias_gradients_of_many_rows(arch, T):
         assert bool((size > 0).all()), key
         assert bool(((got - terms.sum(0)).abs() <= 64 * 2.0 ** -24 * size).all()), key
     ch.close()
+
+
+# Shape, sequences of 50 tokens, and what the projections take by their sizes:
+# (columns of a wave tile, splits of K) of the QKV projection with RoPE and of the
+# output projection's data gradient with delta.
+_HEAD_CASES = [("1b", 4, "split", "split"), ("1b", 22, "64", "64"), ("8b", 4, "split", "split"),
+               ("8b", 12, "128", "128"), ("8b", 60, "128", "large"), ("16", 22, "64", None), ("32", 22, "64", None)]
+
+
+@pytest.mark.parametrize("name,B,qkv,delta", _HEAD_CASES)
+def test_rotation_and_delta_epilogues_by_route(name, B, qkv, delta):
+    """One layer's q|k|v after the rotation, dO, and through delta dq|dk|dv, from
+    the chunk's own operands in fp64, on each kernel that can carry the
+    epilogue: 128 x 128 tiles with 64- and 128-column wave tiles, their last rows
+    partial (200, 600, 1100 and 3000 are no multiples of 32 or 128), the sum of
+    split K, and 256 x 256 tiles.  q|k|v and dO: half a unit of bf16 of the value,
+    plus fp32 sums of K terms (2^-18 of the sum of absolute products).  dq|dk|dv
+    per head: the tolerance of the attention kernels; rows are short (50), so
+    that delta is a large part of dq and dk."""
+    import workload
+    from paper_2608_07974_amd.chunk import TorchChunk, config_from_shape
+    from tests.gemm_route import TILE_128, TILE_128_WIDE, TILE_256, route
+    zl = _zl()
+    base = dict(n_layers=1, batch=B, seq=50, vocab=512, d_ff=512)
+    shp = workload.get_config(name).with_(**base) if name in ("1b", "8b") else workload.get_config("1b").with_(
+        d_model=512, n_heads=512 // int(name), n_kv_heads=128 // int(name), head_dim=int(name), **base)
+    T, d, hd, hq, hkv = 50 * B, shp.d_model, shp.head_dim, shp.n_heads, shp.n_kv_heads
+    dq, nqkv = hq * hd, (hq + 2 * hkv) * hd
+    for want, r in ((qkv, route(T, nqkv, d, 1, 1, heads=True, hd=hd)), (delta, route(T, dq, d, 1, 0, heads=True, hd=hd))):
+        if want:
+            got = "split" if r["nz"] > 1 else {TILE_128: "64", TILE_128_WIDE: "128", TILE_256: "large"}[r["tile"]]
+            assert got == want, r
+    ch = TorchChunk(config_from_shape(shp, alpha=1.0, optimizer="sgd"))
+    gen = torch.Generator(device=_dev()).manual_seed(B + d)
+    ch.master.normal_(0.0, 0.03, generator=gen)
+    ch.head_w.normal_(0.0, 0.02, generator=gen)
+    zl.zl_refresh_shadow(ch.handle, _stream())
+    h = torch.randn(B, 50, d, device=_dev(), generator=gen).to(torch.bfloat16)
+    ch.forward(h)
+    ch.objective(torch.randint(0, 512, (B, 50), device=_dev(), generator=gen).to(torch.int32))
+    ch.backward(1.0, 0)
+    w = torch.cat([ch.view(ch.shadow, "L0." + n).double() for n in ("wq", "wk", "wv")])
+    ang = torch.arange(50, device=_dev()).double()[:, None] * float(np.float32(shp.rope_theta)) ** (
+        -torch.arange(hd // 2, device=_dev()).double() / (hd // 2))
+    cs = torch.cat([ang.cos().float().double()] * 2, 1).repeat(B, 1)[:, None, :]  # [T, 1, hd]
+    sn = torch.cat([-ang.sin().float().double(), ang.sin().float().double()], 1).repeat(B, 1)[:, None, :]
+
+    def rotate(x, sign=1.0):  # the q and k heads of [T, nqkv]
+        y = x.reshape(T, -1, hd).clone()
+        r = y[:, : hq + hkv]
+        y[:, : hq + hkv] = r * cs + sign * torch.roll(r, hd // 2, 2) * sn
+        return y.reshape(T, -1)
+
+    def close(got, ref, size):
+        bad = (got - ref).abs() > 2.0 ** -8 * ref.abs() + 2.0 ** -18 * size
+        assert not bool(bad.any()), (int(bad.sum()), bad.nonzero()[:4].tolist())
+    n1 = ch.inspect_device("n1").double()
+    size = (n1.abs() @ w.abs().t()).reshape(T, -1, hd)
+    got = ch.inspect_device("qkv").double()
+    close(got, rotate(n1 @ w.t()), (size + torch.roll(size, hd // 2, 2)).reshape(T, -1))
+    dxb, wo = ch.inspect_device("dxb").double(), ch.view(ch.shadow, "L0.wo").double()
+    do = ch.inspect_device("do").double()
+    close(do, dxb @ wo, dxb.abs() @ wo.abs())
+    q, k, v = (x.cpu().numpy().reshape(B, 50, -1, hd) for x in got.split([dq, hkv * hd, hkv * hd], 1))
+    _, cache = ops.attention_fwd(q, k, v, np.full(B, 50, np.int32))
+    ref = [torch.tensor(x.reshape(T, -1)).to(_dev()) for x in ops.attention_bwd(do.cpu().numpy().reshape(B, 50, hq, hd), cache)]
+    ref = rotate(torch.cat(ref, 1), -1.0).reshape(T, -1, hd)
+    err = ch.inspect_device("dqkv").double().reshape(T, -1, hd) - ref
+    rel = err.pow(2).sum((0, 2)).sqrt() / ref.pow(2).sum((0, 2)).sqrt()
+    assert float(rel.max()) < 1.2e-2, rel
+    ch.close()
