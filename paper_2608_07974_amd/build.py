@@ -34,7 +34,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # compiler's resource-usage remarks).
 NO_SCRATCH = {"gemm_kk.hip": "gemm_dma_kernel", "gemm_kn.hip": "gemm_dma_kernel",
               "gemm_mn.hip": "gemm_dma_kernel", "gemm_mk.hip": "gemm_dma_kernel",
-              "attention_mfma.hip": "attn_"}
+              "attention_mfma.hip": "attn_", "gemm_skinny.hip": "kernel", "gemm_f32.hip": "kernel",
+              "gemm.hip": "kernel", "rowops.hip": "kernel", "objective.hip": "kernel"}
 
 
 def _scratch_users(stderr, pattern):

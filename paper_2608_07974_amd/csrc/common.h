@@ -40,6 +40,14 @@ __host__ __device__ inline bf16_t f32_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
+// Two values rounded to bf16 (nearest even) by the hardware's packed conversion
+// (as f32_to_bf16, in one instruction instead of a dozen).
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   __device__ static inline float load(const float* p, size_t i) { return p[i]; }

@@ -19,8 +19,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // ---------------------------------------------------------------- epilogue
-__device__ inline float silu_f(float g) { return g / (1.f + __expf(-g)); }
-
 // GELU (tanh form).  (1 + tanh u) / 2 = 1 / (1 + exp(-2u)): one exponential and
 // one division instead of tanhf's branches, and no cancellation in 1 + tanh u
 // at negative u.
@@ -136,13 +134,6 @@ __device__ __forceinline__ void swiglu_bwd8(const float (&da)[EW], const float (
     dg[i] = da[i] * u[i] * dsilu;
     du[i] = da[i] * silu;
   }
-}
-// Two values rounded to bf16 (nearest even) by the hardware's packed conversion
-// (as f32_to_bf16, in one instruction instead of a dozen).
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
 }
 // fp16 of values that are not above zero, saturating (as f32_to_f16; NaN stays NaN).
 __device__ __forceinline__ void stv_f16_neg(void* p, size_t i, const float (&v)[EW]) {

@@ -20,9 +20,9 @@ struct GemmShape {
   int hd;
 };
 
-// Tile size and splits of K, by an estimate of the launch's time from its
-// sizes alone (microseconds; rates measured on the launches of the GPT-2,
-// Llama-1B and 8B shapes at 128 to 16384 tokens):
+// Tile size and splits of K below 240 large tiles, by an estimate of the launch's
+// time from its sizes alone (microseconds; rates fitted to launches of the GPT-2,
+// Llama-1B and 8B shapes at 128 to 16384 tokens, two and three stages deep):
 //  - a 256 x 256 tile has a CU for itself and takes 0.027 per unit of K; its
 //    prologue and epilogue about 12;
 //  - a 128 x 128 tile shares its CU with a second one once there are more
@@ -30,12 +30,14 @@ struct GemmShape {
 //    0.0125 up to 256, in proportion between; ends about 8;
 //  - splitting K over nz blocks writes and reads nz fp32 partials (at about
 //    4 TB/s) and adds the launch that sums them (5).
-// Each split keeps 256 of K (four to eight k tiles) and the partials stay
-// within the workspace.  What it replaced - large tiles from 240 up, 128 x 128
-// split to the next multiple above 256 blocks below that - took two waves of
-// blocks where one does (48 tiles x 6 = 288 blocks: 511 us; x 5: one wave),
-// 192 large tiles as 768 small ones, and 256 x 256 tiles always for the RoPE and
-// delta epilogues (3 - 48 blocks).
+// It ranks the choices, no more: it counts the ends once per launch and knows
+// neither the epilogue's kind nor the deeper pipeline of deep_stages.  No more
+// splits than 256 of K each; split_k rounds their depth up to the k tile, so
+// the last may be shorter and there may be fewer.  The partials stay within the
+// workspace.  What it replaced - 128 x 128 tiles split to the next multiple above
+// 256 blocks - took two waves of blocks where one does (48 tiles x 6 = 288
+// blocks: 511 us; x 5: one wave), 192 large tiles as 768 small ones, and 256 x 256
+// tiles always for the RoPE and delta epilogues (3 - 48 blocks).
 struct GemmPlan {
   bool large;
   int nz;
@@ -145,7 +147,7 @@ GemmRoute route_gemm(const GemmShape& g, F&& dma_ok) {
   const GemmPlan plan = plan_gemm(g);
   GemmRoute r = {plan.large ? TILE_256 : TILE_128, false, plan.nz};
   if (g.heads && !plan.large) {
-    if (!g.ak) r = {TILE_256, false, 1};
+    if (!g.ak) r = {TILE_256, false, 1};  // no projection of the chunk has an MN-major A
     else if (g.hd > 64) r.tile = TILE_128_WIDE;
   }
   r.dma = dma_ok(r.tile == TILE_256 ? 256 : 128);

@@ -127,13 +127,6 @@ __device__ inline void ldz4(const uint16_t* p, int64_t v, float (&x)[4], const f
   x[3] = f16_to_f32((uint16_t)(a.y >> 16)) + mx;
 }
 
-// Two values rounded to bf16 (nearest even) by the hardware's packed conversion.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t pack_bf16(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-}
-
 template <typename ZT>
 __global__ void __launch_bounds__(OT) objective_rows_kernel(ObjDesc o) {
   __shared__ Soft red[OT / 64];
@@ -218,9 +211,10 @@ __global__ void __launch_bounds__(OT) objective_rows_kernel(ObjDesc o) {
     // fp16 cache: 8 columns per lane and step (16-byte loads and stores; they
     // share a 64-column block), two steps in flight.  Bound by HBM (6 bytes
     // per logit) only if the arithmetic is kept short: the constants of a block
-    // are folded, one exponential and about seven other instructions are left
-    // per logit, and the label's column is one uniform test per step.  (8-byte
-    // accesses and one formula per column: 755 us at 4096 x 128256.)
+    // are folded, one exponential (two for the forward KL) and about seven other
+    // instructions are left per logit, and the label's column is one test per 8
+    // columns.  (8-byte accesses and one formula per column: 755 us at 4096 x
+    // 128256.)
     const int V8 = o.V & ~7;
     constexpr float L2E = 1.4426950408889634f;
     const float c1 = a * inv, c2 = zp ? (1.f - a) * inv : 0.f;
