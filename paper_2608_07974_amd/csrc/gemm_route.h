@@ -58,12 +58,18 @@ inline GemmPlan plan_gemm(const GemmShape& g) {
   }
   // From 240 large tiles up that are not mostly padding (an eighth at most; 80
   // rows of logits take 117 us as 1002 small tiles, 147 as 501 large ones) the
-  // estimate decides nothing: large tiles, unless their second round would leave
-  // three quarters of the chip idle (measured at 64 to 6144 of K in the three
-  // layouts: small over large is 0.83 - 0.95 at 288 and 320 tiles, but 1.08 - 1.24
-  // at 240 and 256 of K 256, 1.04 - 1.14 at 376 and 384, 1.03 - 1.15 from 400 up,
-  // and 1.05 - 1.10 at 560 of K 8192 - 16384).
-  if (t256 >= 240 && 2 * t128 >= 7 * t256) return {t256 <= 256 || t256 > 320, 1};
+  // estimate decides nothing: large tiles, unless their last round would leave
+  // three quarters of the chip idle, or half of it at a short K.  Measured at 64 to
+  // 6144 of K in the three layouts, small over large is 0.83 - 0.95 at 288 and 320
+  // tiles; at 376 and 384 0.89 - 1.01 to K 256, 1.04 - 1.14 from 768; at 564 to 640
+  // 0.91 - 0.98 to K 768, 1.00 above and 1.05 - 1.10 at K 8192 - 16384; 1.08 - 1.24 at
+  // 240 and 256 of K 256, 1.03 - 1.15 at 400 to 512 and from 672 up.
+  if (t256 >= 240 && 2 * t128 >= 7 * t256) {
+    const long last = (t256 - 1) % 256 + 1;
+    const bool small = t256 > 256 && t256 <= 640 &&
+                       ((t256 <= 512 && last <= 64) || (last <= 128 && g.K <= (t256 <= 512 ? 256 : 768)));
+    return {!small, 1};
+  }
   GemmPlan best = {true, 1};
   double tb = 0.;
   for (int large = 1; large >= 0; --large) {

@@ -68,13 +68,15 @@ def test_few_columns_of_several_products():
 
 
 def test_from_240_large_tiles_up_tiles_are_large():
-    """Small tiles there only where the second round of large ones is nearly empty."""
+    """Small tiles there only where the last round of large ones is nearly empty,
+    or half empty at a short K."""
+    small = {20: (64, 256, 768, 2048, 8192), 24: (64, 256), 35: (64, 256, 768), 40: (64, 256, 768)}
     for ak, bk in ((1, 1), (1, 0), (0, 0)):
-        for m in (15, 16, 20, 24, 25, 28, 35, 48):  # x 16 large tiles: 240 ... 768
-            for K in (64, 256, 2048, 8192):
+        for m in (15, 16, 20, 24, 25, 28, 35, 40, 42, 48):  # x 16 large tiles: 240 ... 768
+            for K in (64, 256, 768, 2048, 8192):
                 r = route(256 * m, 4096, K, ak, bk)
                 assert r["nz"] == 1
-                assert (r["tile"] == TILE_256) == (m != 20), (m, K)
+                assert (r["tile"] == TILE_128) == (K in small.get(m, ())), (m, K)
         assert route(80, 128256, 2048, ak, bk, 0, False)["tile"] == TILE_128  # half of a large tile is padding
 
 
