@@ -27,8 +27,8 @@ def _stream():
 
 
 # bf16 operands with contiguous M need M % 8 == 0 (16-byte rows; the library
-# rejects the rest, tested on the CPU); the fp32 SIMT path is sized for small
-# problems, so it is not run at 4096 x 3848.
+# rejects the rest, tested on the CPU); fp32 is a configuration of small shapes
+# and not run at 4096 x 3848 (its two kernels by size: test_gemm_f32_tiles).
 _LAYOUT_CASES = [(dt, lay, M, N, K)
                  for dt in ("bf16", "f32") for lay in ("nt", "nn", "tn")
                  for M, N, K in ((8, 8, 8), (1, 8, 8), (304, 520, 200), (129, 136, 1000),
